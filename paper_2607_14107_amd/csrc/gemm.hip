@@ -2,35 +2,36 @@
 // (Sec. 4.1: re-project the stale rows and the active block; Corollary 1 of
 // App. B: K = W_K h, V = W_V h) and of the Q projection of the active block.
 //
-// The product is skinny: a few hundred gathered rows times a [N][K] weight
-// that is read once from HBM.  Two kernels:
+// The rows are a few tens to a few thousand gathered ones, the [N][K] weight
+// is read from HBM.  Four kernels, picked by gemm_plan:
 //
-// gemm_rows_kernel (more than 64 rows): a workgroup of 4 waves owns
+// gemm_tile_kernel (bf16, more than 64 rows; tile_body in gemm_dev.hpp):
+//   64 to 256 rows x 128 to 256 columns per workgroup, both operands by DMA.
+//
+// gemm_rows_kernel (fp32, more than 64 rows): a workgroup of 4 waves owns
 //   BM = 32*MT rows and 128 columns; wave w computes all BM rows of columns
-//   32w..32w+31 with v_mfma_f32_32x32x16_bf16 (on gfx950 it does twice the
-//   work per issue slot of the 16x16x32 form).  Per super-step of 256 bytes
-//   of K:
+//   32w..32w+31 with v_mfma_f32_32x32x2_f32.  Per super-step of 256 bytes of
+//   K:
 //   - the gathered input rows are staged in LDS (16-byte coalesced loads,
 //     272-byte row pitch: conflict-free MFMA reads) and shared by the waves;
-//     a wave reads the fragments of the next 16-k chunk while the MFMAs of
-//     the current one run;
+//     a wave reads the fragments of the next chunk while the MFMAs of the
+//     current one run;
 //   - each wave streams its weight rows from HBM straight into registers,
 //     128 contiguous bytes per lane, two super-steps ahead (triple buffer,
 //     loop unrolled three times so the buffers rotate without copies).
 //   A row's (sequence, position) is one load away (fixed stride of
 //   k_max + block_len rows per sequence), so the first input rows follow
 //   the weight prefetch closely.
-//   When rows x columns do not fill the chip, K is split over workgroups;
-//   each writes its fp32 partial tile as one contiguous block of the
-//   workspace ([split][column tile][row][128]: long DRAM bursts, not 512-byte
-//   pieces 32 KB apart), the row map goes next to it, and gemm_reduce_kernel
+//
+// Where rows x columns do not fill the chip, K is split over workgroups; each
+//   writes its fp32 partial tile to the workspace ([split][column
+//   tile][row][128]), the row map goes next to it, and gemm_reduce_kernel
 //   sums the partials in split order (deterministic) and scatters 16-byte
 //   rows.
 //
-// gemm_dma_kernel (65 to 320 rows, e.g. the refresh of one sequence's stale
-//   rows and block, or the Q projection of a batch's blocks; up to 1280 rows
-//   for outputs of at most 1024 columns): one of up to two row tiles (eight
-//   for narrow outputs) of up to 160 rows and 128 columns per workgroup, both operands
+// gemm_dma_kernel (17 to 256 rows, e.g. the refresh of one sequence's stale
+//   rows and block, or the Q projection of a batch's blocks): one of up to two
+//   row tiles of up to 160 rows and 128 columns per workgroup, both operands
 //   (bf16) brought into LDS by global_load_lds_dwordx4 (no VGPR staging, so the
 //   weight loads never wait behind registers that MFMAs still read), in
 //   stages of 128 bytes of each row; four LDS slots, three stages in flight,
@@ -41,8 +42,8 @@
 //   for the DMA are explicit s_waitcnt immediates (each wave issues the same
 //   number of DMA instructions per stage), and each slot's LDS arrays are
 //   separate objects so the compiler does not add waits of its own.
-//   Measured on the batch-1 LLaDA-8B refresh (138 rows x 8192 x 4096): 18.6 us for
-//   the split-K GEMM against 25.9 us for gemm_rows_kernel.
+//   Measured on the batch-1 LLaDA-8B refresh (138 rows x 8192 x 4096): 21.5 us
+//   for the split-K GEMM.
 //
 // gemm_small_kernel (at most 64 rows, e.g. the Q projection): a workgroup
 //   owns all rows and 16 columns; its 4 waves take interleaved super-steps
@@ -50,9 +51,10 @@
 //   summed in LDS, so no partials leave the chip.  A load instruction covers
 //   64 contiguous bytes of each of 16 rows.
 //
-// In both, A and B use the same lane -> k assignment, so k may be visited in
+// In all, A and B use the same lane -> k assignment, so k may be visited in
 // any order.  All loads are unconditional (rows or columns past the end read
 // row 0 and are never stored) so the compiler's wait counts stay static.
+#include <algorithm>
 #include <mutex>
 
 #include "gemm_dev.hpp"
@@ -63,23 +65,16 @@ namespace {
 
 constexpr int kLda = 272;         // LDS row pitch (bytes) of the staged input rows
 constexpr int kTargetWgs = 256;   // one workgroup per compute unit on MI355X
-// Per-CU rate of a 192-row tile relative to a 256-row one in the plan's
-// estimate.  Unsplit, the batch-8 LLaDA-8B refresh (1488 x 8192 x 4096 in
-// one round) measures 0.86 (256 tiles of 192 rows 112.9 us against 192 of
-// 256 rows 130 us); 0.95 is the value whose choices matched the faster
-// plan on every shape measured through polestar_linear (with 0.86 the
-// 1250 x 2512 x 2048 product takes 256-row tiles in four splits, 45.4 us,
-// against 43.8 us for 192-row tiles in two).
-constexpr double kTile192Rate = 0.95;
 
 // ---------------------------------------------------------------------------
 // gemm_rows_kernel: BM = 32*MT rows x 128 columns per workgroup; wave w owns
-// columns 32w..32w+31 of all rows (v_mfma_f32_32x32x16_bf16: lane l carries
-// row/column l%32 and k-group l/32, 128 contiguous bytes per super-step).
+// columns 32w..32w+31 of all rows (lane l carries row/column l%32 and k-group
+// l/32, 128 contiguous bytes per super-step).
 // ---------------------------------------------------------------------------
 
-template <bool BF16, int MT>
+template <int MT>
 __global__ __launch_bounds__(kGemmBlock) void gemm_rows_kernel(GemmArgs g) {
+    constexpr bool BF16 = false;
     using T = Elem<BF16>;
     constexpr int BM = MT * 32;
     constexpr int BN = 128;
@@ -251,13 +246,15 @@ __global__ __launch_bounds__(kGemmBlock) void gemm_rows_kernel(GemmArgs g) {
 // gemm_dma_kernel: the DMA-staged body of gemm_dev.hpp (dma_body).
 // ---------------------------------------------------------------------------
 
-template <bool BF16, int MT, int NST, bool NTW>
+template <int MT, int NST, bool NTW>
 __global__ __launch_bounds__(kGemmBlock) void gemm_dma_kernel(GemmArgs g) {
-    dma_body<BF16, MT, NST, 4, NTW>(g, blockIdx.x);
+    dma_body<true, MT, NST, 4, NTW>(g, blockIdx.x);
 }
 
 template <int MI, int NJ>
-__global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) { tile_body<MI, NJ>(g, blockIdx.x); }
+__global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) {
+    tile_body<MI, NJ>(g, blockIdx.x);
+}
 
 // Sum of the split-K partials, in split order (deterministic): thread ->
 // (column tile, row, 8 columns) so that consecutive threads read consecutive
@@ -265,7 +262,7 @@ __global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) { t
 // loads are independent, then one rounded 16-byte store.
 template <bool BF16>
 __global__ __launch_bounds__(kGemmBlock) void gemm_reduce_kernel(GemmArgs g) {
-    reduce_body<BF16>(g, blockIdx.x);
+    reduce_body<BF16>(g, static_cast<long>(blockIdx.x) * kGemmBlock + threadIdx.x);
 }
 
 template <bool BF16, int MT>
@@ -273,63 +270,61 @@ __global__ __launch_bounds__(kSmallBlock) void gemm_small_kernel(GemmArgs g) {
     small_body<BF16, MT>(g, blockIdx.x, blockIdx.y);
 }
 
-template <bool BF16, int MT>
-void launch_rows(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_rows_kernel<BF16, MT>), dim3(p.grid), dim3(kGemmBlock), 0, s, g);
-}
-
-template <bool BF16>
 bool dispatch_rows(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
-    switch (p.mt) {   // 32-row tiles per workgroup
-        case 1: launch_rows<BF16, 1>(p, g, s); return true;
-        case 2: launch_rows<BF16, 2>(p, g, s); return true;
-        case 3: launch_rows<BF16, 3>(p, g, s); return true;
-        case 4: launch_rows<BF16, 4>(p, g, s); return true;
-        case 5: launch_rows<BF16, 5>(p, g, s); return true;
-        case 6: launch_rows<BF16, 6>(p, g, s); return true;
-        case 7: launch_rows<BF16, 7>(p, g, s); return true;
-        case 8: launch_rows<BF16, 8>(p, g, s); return true;
-        default: return false;
-    }
-}
-
-template <bool BF16, int NST, bool NTW>
-bool dispatch_dma_mt(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
     const dim3 grid(p.grid), block(kGemmBlock);
-    switch (p.mt) {   // 16-row tiles
-        case 2: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 2, NST, NTW>), grid, block, 0, s, g); return true;
-        case 3: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 3, NST, NTW>), grid, block, 0, s, g); return true;
-        case 4: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 4, NST, NTW>), grid, block, 0, s, g); return true;
-        case 5: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 5, NST, NTW>), grid, block, 0, s, g); return true;
-        case 6: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 6, NST, NTW>), grid, block, 0, s, g); return true;
-        case 7: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 7, NST, NTW>), grid, block, 0, s, g); return true;
-        case 8: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 8, NST, NTW>), grid, block, 0, s, g); return true;
-        case 9: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 9, NST, NTW>), grid, block, 0, s, g); return true;
-        case 10: hipLaunchKernelGGL((gemm_dma_kernel<BF16, 10, NST, NTW>), grid, block, 0, s, g); return true;
+    switch (p.mt) {   // 32-row tiles per workgroup
+        case 1: hipLaunchKernelGGL(gemm_rows_kernel<1>, grid, block, 0, s, g); return true;
+        case 2: hipLaunchKernelGGL(gemm_rows_kernel<2>, grid, block, 0, s, g); return true;
+        case 3: hipLaunchKernelGGL(gemm_rows_kernel<3>, grid, block, 0, s, g); return true;
+        case 4: hipLaunchKernelGGL(gemm_rows_kernel<4>, grid, block, 0, s, g); return true;
+        case 5: hipLaunchKernelGGL(gemm_rows_kernel<5>, grid, block, 0, s, g); return true;
+        case 6: hipLaunchKernelGGL(gemm_rows_kernel<6>, grid, block, 0, s, g); return true;
+        case 7: hipLaunchKernelGGL(gemm_rows_kernel<7>, grid, block, 0, s, g); return true;
+        case 8: hipLaunchKernelGGL(gemm_rows_kernel<8>, grid, block, 0, s, g); return true;
         default: return false;
     }
 }
 
-template <bool BF16>
+template <int MT, bool NTW>
+bool dispatch_dma_nst(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
+    const dim3 grid(p.grid), block(kGemmBlock);
+    switch (2 * p.steps_per_split) {   // 128-byte stages per split
+        case 8: hipLaunchKernelGGL((gemm_dma_kernel<MT, 8, NTW>), grid, block, 0, s, g); return true;
+        case 16: hipLaunchKernelGGL((gemm_dma_kernel<MT, 16, NTW>), grid, block, 0, s, g); return true;
+        default: break;
+    }
+    if constexpr (MT > 4) {            // 17..64 rows split K into 8 or 16 stages only
+        switch (2 * p.steps_per_split) {
+            case 10: hipLaunchKernelGGL((gemm_dma_kernel<MT, 10, NTW>), grid, block, 0, s, g); return true;
+            case 12: hipLaunchKernelGGL((gemm_dma_kernel<MT, 12, NTW>), grid, block, 0, s, g); return true;
+            case 14: hipLaunchKernelGGL((gemm_dma_kernel<MT, 14, NTW>), grid, block, 0, s, g); return true;
+            default: break;
+        }
+    }
+    return false;
+}
+
+// One row tile of 17..160 rows (it reads every weight byte once: non-temporal
+// weight stream) or two of 81..128.
 bool dispatch_dma(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
-    static_assert(kDmaMaxRowTiles == 10, "dispatch covers 2..kDmaMaxRowTiles");
-    // one row tile reads every weight byte once: non-temporal weight stream
     if (p.row_tiles == 1) {
-        switch (2 * p.steps_per_split) {   // 128-byte stages per split
-            case 8: return dispatch_dma_mt<BF16, 8, true>(p, g, s);
-            case 10: return dispatch_dma_mt<BF16, 10, true>(p, g, s);
-            case 12: return dispatch_dma_mt<BF16, 12, true>(p, g, s);
-            case 14: return dispatch_dma_mt<BF16, 14, true>(p, g, s);
-            case 16: return dispatch_dma_mt<BF16, 16, true>(p, g, s);
+        switch (p.mt) {   // 16-row tiles
+            case 2: return dispatch_dma_nst<2, true>(p, g, s);
+            case 3: return dispatch_dma_nst<3, true>(p, g, s);
+            case 4: return dispatch_dma_nst<4, true>(p, g, s);
+            case 5: return dispatch_dma_nst<5, true>(p, g, s);
+            case 6: return dispatch_dma_nst<6, true>(p, g, s);
+            case 7: return dispatch_dma_nst<7, true>(p, g, s);
+            case 8: return dispatch_dma_nst<8, true>(p, g, s);
+            case 9: return dispatch_dma_nst<9, true>(p, g, s);
+            case 10: return dispatch_dma_nst<10, true>(p, g, s);
             default: return false;
         }
     }
-    switch (2 * p.steps_per_split) {
-        case 8: return dispatch_dma_mt<BF16, 8, false>(p, g, s);
-        case 10: return dispatch_dma_mt<BF16, 10, false>(p, g, s);
-        case 12: return dispatch_dma_mt<BF16, 12, false>(p, g, s);
-        case 14: return dispatch_dma_mt<BF16, 14, false>(p, g, s);
-        case 16: return dispatch_dma_mt<BF16, 16, false>(p, g, s);
+    switch (p.mt) {
+        case 6: return dispatch_dma_nst<6, false>(p, g, s);
+        case 7: return dispatch_dma_nst<7, false>(p, g, s);
+        case 8: return dispatch_dma_nst<8, false>(p, g, s);
         default: return false;
     }
 }
@@ -348,9 +343,159 @@ bool dispatch_small(const GemmPlan& p, const GemmArgs& g, hipStream_t s) {
 
 }  // namespace
 
-// Partial tiles of a split-K plan, [ksplit][col_tiles][m_max][128] fp32.
-static size_t partial_bytes(const GemmPlan& p, long m_max) {
-    return align_up(static_cast<size_t>(p.ksplit) * p.col_tiles * m_max * 128 * sizeof(float), 256);
+// Scratch of a split-K product: the partial tiles [ksplit][col_tiles][m_max][128]
+// fp32 and the row map.
+static size_t partial_bytes(int ksplit, long m_max, int N) {
+    return align_up(static_cast<size_t>(ksplit) * ceil_div(N, 128) * m_max * 128 * sizeof(float), 256);
+}
+static size_t split_bytes(int ksplit, long m_max, int N) {
+    if (ksplit == 1) return 0;
+    return partial_bytes(ksplit, m_max, N) + align_up(static_cast<size_t>(m_max) * 2 * sizeof(int), 256);
+}
+
+// The split that the workspace sizes are quoted for.  The sizes are part of the
+// interface (callers keep buffers of them, and a call with less is refused, as
+// is one beyond polestar_refresh_kv_noalloc's array), so they follow this rule
+// and not the kernels: a plan may split less than it, never more.  It prices
+// 256- and 192-sided tiles at 3.9 GFLOP/ms per CU in rounds of 256 and the
+// partials at 5 TB/s; fewer rows, narrow outputs and shapes too small for that
+// count 128-column tiles of at most 160 or 256 rows.
+static int quoted_split(bool bf16, long m_max, int N, int K) {
+    const int nsteps = ceil_div(K, bf16 ? 128 : 64);
+    const long col_tiles = ceil_div(N, 128);
+    auto even_steps = [nsteps](int ks) { return nsteps % ks == 0 && nsteps / ks >= 4 && nsteps / ks <= 8; };
+    if (m_max <= 64) {
+        for (int ks = ceil_div(kTargetWgs, col_tiles); bf16 && m_max > 16 && ks <= kMaxSplit; ++ks)
+            if (nsteps % ks == 0 && (nsteps / ks == 4 || nsteps / ks == 8)) return ks;
+        return 1;
+    }
+    bool narrow = false;
+    for (int ks = 1; ks <= kMaxSplit; ++ks) narrow |= even_steps(ks);
+    narrow = narrow && bf16 && N <= 1024 && m_max <= 1280;
+    if (bf16 && m_max > 160 && K % 64 == 0 && !narrow) {
+        const int nstage = K / 32;
+        int ksplit = 1, rows_tile = 256;
+        long tiles = static_cast<long>(ceil_div(m_max, 256)) * ceil_div(N, 256);
+        double best = 1e30;
+        for (int rows = 256; rows >= 192; rows -= 64) {
+            for (int cols = 256; cols >= 192; cols -= 64) {
+                const long n = static_cast<long>(ceil_div(m_max, rows)) * ceil_div(N, cols);
+                const double rate = (rows == 256 ? 1.0 : 0.95) * (cols == 256 ? 1.0 : 0.95);
+                const double tile_us = static_cast<double>(rows) * cols * 2.0 * K / (3.9e6 * rate);
+                for (int k = 1; k <= kMaxSplit; ++k) {
+                    if (nstage % (4 * k) != 0 || nstage / k < 16) continue;
+                    const double rounds = static_cast<double>((n * k + kTargetWgs - 1) / kTargetWgs);
+                    const double cost = rounds * tile_us / k + (k > 1 ? 8.0 * k * m_max * N / 5e6 : 0.0);
+                    if (cost < best) {
+                        best = cost;
+                        ksplit = k;
+                        rows_tile = rows;
+                        tiles = n;
+                    }
+                }
+            }
+        }
+        if (tiles * ksplit >= kTargetWgs / 2 &&
+            (ksplit <= 4 || nstage / ksplit >= 48 || ceil_div(m_max, rows_tile) >= 4))
+            return ksplit;
+    }
+    if (bf16 && (m_max <= 320 || narrow)) {
+        const long tiles = ceil_div(m_max, 160L) * col_tiles;
+        long best = -1;
+        int ksplit = 0;
+        for (int ks = 1; ks <= kMaxSplit; ++ks) {
+            if (!even_steps(ks)) continue;
+            const long cost = (tiles * ks + kTargetWgs - 1) / kTargetWgs * (nsteps / ks);
+            if (best < 0 || cost < best) {
+                best = cost;
+                ksplit = ks;
+            }
+        }
+        if (ksplit > 0) return ksplit;
+    }
+    const long tiles = ceil_div(m_max, bf16 && (m_max <= 320 || narrow) ? 160L : 256L) * col_tiles;
+    const int ks = std::min<long>(std::min(kMaxSplit, nsteps), tiles < kTargetWgs ? ceil_div(kTargetWgs, tiles) : 1);
+    return ceil_div(nsteps, ceil_div(nsteps, ks));
+}
+
+// Estimated time (us) of the tile kernel with `tiles` tiles of 32 mi x 64 nj in
+// ks splits of `steps` K tiles: ceil(tiles * ks / 256) rounds of one workgroup
+// per CU, each a fixed cost (launch, row map, first DMA, stores) and its K
+// tiles at the shape's time, measured with every CU busy (12288 x 8192 x
+// 4096); a split run adds the reduction's launch and its fp32 partials
+// written and read back (512 x 4096 x 4096 in 2 and 4 splits, 512 x 4096 x
+// 12288 in 4 and 8).
+static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_max, int N) {
+    double kt = 0.0;
+    switch (10 * mi + nj) {
+        case 84: kt = 1.52; break;
+        case 83: kt = 1.25; break;
+        case 64: kt = 1.27; break;
+        case 82: kt = 0.87; break;
+        case 44: kt = 0.89; break;
+        case 63: kt = 0.93; break;
+        case 62: kt = 0.67; break;
+        case 43: kt = 0.71; break;
+        case 42: kt = 0.53; break;
+        case 24: kt = 0.70; break;
+        default: kt = 0.42; break;
+    }
+    const double rounds = static_cast<double>((tiles * ks + kTargetWgs - 1) / kTargetWgs);
+    return rounds * (steps * kt + 4.0) + (ks > 1 ? 5.0 + 4.0 * ks * m_max * N * 0.28e-6 : 0.0);
+}
+
+// The tile kernel's plan: the tile shape and split with the least estimated
+// time among splits up to max_split, the larger tile and the smaller split on
+// ties.  Every split runs an even number of K tiles and at least eight.
+static void plan_tile(GemmPlan& p, long m_max, int N, int K, int max_split) {
+    const int nkt = K / 64;                              // K tiles, an even number
+    double best = 1e30;
+    for (int mi = 8; mi >= 2; mi -= 2) {
+        for (int nj = 4; nj >= 2; --nj) {
+            if (mi == 2 && nj == 3) continue;            // not instantiated
+            const long tiles = static_cast<long>(ceil_div(m_max, 32 * mi)) * ceil_div(N, 64 * nj);
+            for (int ks = 1; ks <= max_split; ++ks) {
+                if (ks > 1 && tiles * (ks - 1) >= kTargetWgs) break;   // already a full round
+                const int steps = 2 * ceil_div(nkt / 2, ks);
+                if (ceil_div(nkt, steps) != ks || (ks > 1 && steps < 8)) continue;
+                const double cost = tile_cost(mi, nj, tiles, ks, steps, m_max, N);
+                if (cost < best) {
+                    best = cost;
+                    p.ksplit = ks;
+                    p.tile_mi = mi;
+                    p.tile_nj = nj;
+                    p.steps_per_split = steps;
+                }
+            }
+        }
+    }
+    p.tile = true;
+    p.mt = 2 * p.tile_mi;
+    p.col_tiles = ceil_div(N, 128);                      // of the partials
+    p.row_tiles = ceil_div(m_max, 32 * p.tile_mi);
+    p.grid = static_cast<int>(static_cast<long>(p.row_tiles) * ceil_div(N, 64 * p.tile_nj) * p.ksplit);
+}
+
+// The DMA kernel's plan for 65 to 256 rows: row tiles of at most 160 rows, K
+// split evenly into 8 to 16 stages of 128 bytes per row; the split with the
+// fewest stages in one round of one workgroup per CU.  False when no split
+// does.
+static bool plan_dma(GemmPlan& p, long m_max, int N, int K, int max_split) {
+    const int nsteps = K / 128;
+    const int row_tiles = ceil_div(m_max, 16L * kDmaMaxRowTiles), col_tiles = ceil_div(N, 128);
+    for (int ks = max_split; ks >= 1; --ks) {
+        if (nsteps % ks != 0 || nsteps / ks < 4 || nsteps / ks > 8) continue;
+        if (static_cast<long>(row_tiles) * col_tiles * ks > kTargetWgs) continue;
+        p.dma = true;
+        p.ksplit = ks;
+        p.steps_per_split = nsteps / ks;
+        p.row_tiles = row_tiles;
+        p.col_tiles = col_tiles;
+        p.mt = ceil_div(ceil_div(m_max, row_tiles), 16);
+        p.grid = row_tiles * col_tiles * ks;
+        return true;
+    }
+    return false;
 }
 
 GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
@@ -358,12 +503,14 @@ GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
     const int ks = bf16 ? 128 : 64;
     const int nsteps = ceil_div(K, ks);
     if (m_max <= 0) m_max = 1;
+    const int quoted = quoted_split(bf16, m_max, N, K);
+    p.ws_bytes = split_bytes(quoted, m_max, N);
+    if (!gemm_k_ok(bf16, K)) return p;   // only its size is asked for
     // 17..64 rows (bf16): the DMA kernel with split-K partials streams each
     // weight once with its A rows shared through LDS, where the small kernel
     // re-reads the rows once per 16 columns (the 32-row LLaDA-8B block
     // projection: 12.4 against 13.7 us with the reduce, 64 rows 13.6 against
-    // 21.0); other shapes, or when K does not split into 8 or 16 stages, the
-    // small kernel
+    // 21.0);
     if (m_max <= 64 && bf16 && m_max > 16) {
         const int col_tiles = ceil_div(N, 128);
         for (int ks = ceil_div(kTargetWgs, col_tiles); ks <= kMaxSplit; ++ks) {
@@ -375,12 +522,12 @@ GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
                 p.steps_per_split = nsteps / ks;
                 p.mt = ceil_div(m_max, 16);
                 p.grid = col_tiles * ks;
-                if (ks > 1)
-                    p.ws_bytes = partial_bytes(p, m_max) + align_up(static_cast<size_t>(m_max) * 2 * sizeof(int), 256);
                 return p;
             }
         }
     }
+    // others, or when K does not split into 8 or 16 stages, the small kernel
+    // (their quoted workspace is none, so nothing else could split K)
     if (m_max <= 64) {
         p.small = true;
         p.mt = ceil_div(m_max, 16);
@@ -391,94 +538,27 @@ GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
         p.grid = p.col_tiles;
         return p;
     }
-    p.small = false;
-    p.col_tiles = ceil_div(N, 128);                     // split-K partials: 128-column tiles
-    // Tile kernel: more rows than one DMA tile; 256- or 192-row x 256- or 192-column tiles, K split
-    // while the tiles alone leave compute units idle.  Measured against the
-    // other kernels it wins when it launches at least 128 workgroups and at
-    // most four splits fill the chip, each split still runs 48 stages or
-    // more, or there are four row tiles or more; short splits of one or two
-    // row tiles (256 or 512 rows of a 4096 x 4096 projection) stay on the DMA
-    // or row kernel.
-    // Narrow outputs (at most 1024 columns: four 256-wide tiles across) take
-    // the DMA kernel's 128-column tiles instead, up to eight row tiles: the
-    // Dream-7B refresh (1052 rows x 1024 x 3584) runs 56 tiles in four splits
-    // (224 workgroups, 17 MB of partials) in 27.7 us, where the tile kernel's
-    // 20 tiles needed seven splits (30 MB of partials) and 37.5 us.
-    // Only where the DMA kernel can take K: some split into 4 to 8 steps of
-    // 256 bytes (K = 2816, 22 steps, has none and stays on the tile kernel).
-    bool dma_k = false;
-    for (int ks = 1; ks <= kMaxSplit && !dma_k; ++ks) dma_k = nsteps % ks == 0 && nsteps / ks >= 4 && nsteps / ks <= 8;
-    const bool narrow_dma = bf16 && dma_k && N <= 4 * kTileDim && m_max <= 8L * 16 * kDmaMaxRowTiles;
-    if (bf16 && m_max > 16L * kDmaMaxRowTiles && K % kTileStage == 0 && !narrow_dma) {
-        const int nstage = K / (kTileStage / 2);
-        // The tile shape and split with the least estimated time: ceil(tiles
-        // * k / 256) rounds of one workgroup per CU, each 1/k of a tile's
-        // work (a whole 256 x 256 x K tile at the ~1 PFLOP/s this kernel
-        // sustains: 3.9 GFLOP/ms per CU; a 192-row or 192-column tile at
-        // kTile192Rate of that rate, 192 x 192 at its square), plus the fp32
-        // partials of a split run written and read back (8 k M N bytes at
-        // ~5 TB/s); ties keep the larger tile, rows before columns.
-        // Measured on the batch-8 LLaDA-8B refresh: 192 tiles of 256 rows
-        // (10% stale) unsplit in one round 130 us, in two splits (384
-        // workgroups, a round and a half, 98 MB of partials) 159 us, as 256
-        // tiles of 192 rows 112.9 us; 64 tiles (2%) best in four splits; 20
-        // tiles (the Dream-7B refresh) in seven.  Through polestar_linear the
-        // 192-row plans it picks ran 3-15% faster than the best 256-row ones
-        // (512 x 4096 x 4096: 47.6 against 50.9 us; 1264 x 8192 x 4096: 95.1
-        // against 110.3 us).  Every split runs a whole number of 4-stage loop
-        // trips and at least 16 stages.  192-column tiles moved the 512-row
-        // projections of a 32-layer stack's block-only forwards (12288 and
-        // 24576 columns) from 192 to 256 workgroups: those forwards 13.9 ->
-        // 13.4 ms.
-        int ksplit = 1, mi = 4, nj = 4;
-        double best = 1e30;
-        for (int cm = 4; cm >= 3; --cm) {
-            for (int cn = 4; cn >= 3; --cn) {
-                const int rows = 64 * cm, cols = 64 * cn;
-                const long tiles = static_cast<long>(ceil_div(m_max, rows)) * ceil_div(N, cols);
-                const double rate = (cm == 4 ? 1.0 : kTile192Rate) * (cn == 4 ? 1.0 : kTile192Rate);
-                const double tile_us = static_cast<double>(rows) * cols * 2.0 * K / (3.9e6 * rate);
-                for (int k = 1; k <= kMaxSplit; ++k) {
-                    if (nstage % (4 * k) != 0 || nstage / k < 16) continue;
-                    const double rounds = static_cast<double>((tiles * k + kTargetWgs - 1) / kTargetWgs);
-                    const double cost = rounds * tile_us / k + (k > 1 ? 8.0 * k * m_max * N / 5e6 : 0.0);
-                    if (cost < best) {
-                        best = cost;
-                        ksplit = k;
-                        mi = cm;
-                        nj = cn;
-                    }
-                }
-            }
-        }
-        p.tile_mi = mi;
-        p.tile_nj = nj;
-        p.row_tiles = ceil_div(m_max, 64 * mi);
-        const long tiles = static_cast<long>(p.row_tiles) * ceil_div(N, 64 * nj);
-        p.tile = tiles * ksplit >= kTargetWgs / 2 &&
-                 (ksplit <= 4 || nstage / ksplit >= 48 || p.row_tiles >= 4);
-        p.ksplit = ksplit;
-    }
-    if (p.tile) {
-        const int nstage = K / (kTileStage / 2);
-        const long tiles = static_cast<long>(p.row_tiles) * ceil_div(N, 64 * p.tile_nj);
-        const int ksplit = p.ksplit;
-        p.steps_per_split = nstage / ksplit;
-        p.mt = 2 * p.tile_mi;
-        p.grid = static_cast<int>(tiles * ksplit);
-        if (p.ksplit > 1)
-            p.ws_bytes = partial_bytes(p, m_max) + align_up(static_cast<size_t>(m_max) * 2 * sizeof(int), 256);
+    // bf16 above that: the tile kernel, but for two ranges that the DMA kernel
+    // runs in one round:
+    // - 65 to 160 rows (one row tile) of at least 64 MB of weights, whose
+    //   stream it marks non-temporal: a batch-1 LLaDA-8B layer (138 x 8192 x
+    //   4096) on weights that are not cached 21.5 us against 23.8 for the tile
+    //   kernel, and the kernels after it find more of theirs in the caches
+    //   (57.5 against 61.8 us per layer step); smaller weights are 5-25%
+    //   faster on the tile kernel (160 x 4096 x 4096: 24.3 against 18.7 us);
+    // - 161 to 256 rows of K >= 1536 in two row tiles (4096 x 4096: 176 rows
+    //   20.3 against 24.2 us, 224 rows 22.7 / 25.5, 256 rows 27.2 / 26.1; with
+    //   K = 1024 and below the tile kernel is 10-45% faster).
+    if (bf16) {
+        const bool dma_rows = m_max <= 160 ? m_max > 64 && static_cast<long>(N) * K >= 1L << 25
+                                           : m_max <= 256 && K >= 1536;
+        if (!(dma_rows && plan_dma(p, m_max, N, K, quoted))) plan_tile(p, m_max, N, K, quoted);
         return p;
     }
-    // DMA kernel: up to two row tiles of at most 160 rows (eight for narrow
-    // outputs), K split evenly
-    // into 8 to 16 stages of 128 bytes per row; the split with the fewest
-    // rounds of one workgroup per CU times stages per split, the smaller
-    // split on ties (the Dream-7B Q projection, 56 tiles of K = 3584: four
-    // splits of 14 stages in one round rather than seven of 8 in two)
-    const bool dma_rows = bf16 && (m_max <= 2L * 16 * kDmaMaxRowTiles || narrow_dma);
-    p.row_tiles = dma_rows ? ceil_div(m_max, 16L * kDmaMaxRowTiles) : ceil_div(m_max, 256);
+    // fp32: the row kernel, 256-row tiles of 128 columns, K split to fill one
+    // round of workgroups
+    p.col_tiles = ceil_div(N, 128);
+    p.row_tiles = ceil_div(m_max, 256);
     const long tiles = static_cast<long>(p.row_tiles) * p.col_tiles;
     int ksplit = 1;
     if (tiles < kTargetWgs) ksplit = ceil_div(kTargetWgs, tiles);
@@ -486,23 +566,8 @@ GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
     if (ksplit > nsteps) ksplit = nsteps;
     p.steps_per_split = ceil_div(nsteps, ksplit);
     p.ksplit = ceil_div(nsteps, p.steps_per_split);
-    p.dma = false;
-    long best = -1;
-    for (int ks = 1; dma_rows && ks <= kMaxSplit; ++ks) {
-        if (nsteps % ks != 0 || nsteps / ks < 4 || nsteps / ks > 8) continue;
-        const long cost = (tiles * ks + kTargetWgs - 1) / kTargetWgs * (nsteps / ks);
-        if (best < 0 || cost < best) {
-            best = cost;
-            p.dma = true;
-            p.ksplit = ks;
-            p.steps_per_split = nsteps / ks;
-        }
-    }
-    if (!p.dma) p.row_tiles = ceil_div(m_max, 256);
-    p.mt = p.dma ? ceil_div(ceil_div(m_max, p.row_tiles), 16) : ceil_div(m_max, 32L * p.row_tiles);
+    p.mt = ceil_div(m_max, 32L * p.row_tiles);
     p.grid = static_cast<int>(static_cast<long>(p.row_tiles) * p.col_tiles * p.ksplit);
-    if (p.ksplit > 1)
-        p.ws_bytes = partial_bytes(p, m_max) + align_up(static_cast<size_t>(m_max) * 2 * sizeof(int), 256);
     return p;
 }
 
@@ -532,7 +597,7 @@ GemmArgs refresh_gemm_args(int batch, int seq, int d, int kvd, const void* h_cur
 }
 
 void gemm_finalize_args(const GemmPlan& p, GemmArgs& g) {
-    g.rowmap = p.ksplit > 1 ? reinterpret_cast<int*>(reinterpret_cast<char*>(g.ws) + partial_bytes(p, g.m_max))
+    g.rowmap = p.ksplit > 1 ? reinterpret_cast<int*>(reinterpret_cast<char*>(g.ws) + partial_bytes(p.ksplit, g.m_max, g.N))
                             : nullptr;
     g.ksplit = p.ksplit;
     g.steps_per_split = p.steps_per_split;
@@ -549,10 +614,10 @@ int gemm_reduce_blocks(const GemmPlan& p, const GemmArgs& g) {
 static bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream) {
     const dim3 grid(p.grid), block(kTileThreads);
     switch (10 * p.tile_mi + p.tile_nj) {
-        case 44: hipLaunchKernelGGL((gemm_tile_kernel<4, 4>), grid, block, 0, stream, g); return true;
-        case 43: hipLaunchKernelGGL((gemm_tile_kernel<4, 3>), grid, block, 0, stream, g); return true;
-        case 34: hipLaunchKernelGGL((gemm_tile_kernel<3, 4>), grid, block, 0, stream, g); return true;
-        case 33: hipLaunchKernelGGL((gemm_tile_kernel<3, 3>), grid, block, 0, stream, g); return true;
+#define PS_CASE(MI, NJ) \
+        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_tile_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
+        PS_TILE_SHAPES(PS_CASE)
+#undef PS_CASE
         default: return false;
     }
 }
@@ -562,10 +627,9 @@ polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t s
     bool ok;
     if (p.small) ok = bf16 ? dispatch_small<true>(p, g, stream) : dispatch_small<false>(p, g, stream);
     else if (p.tile) {
-        ok = bf16 && p.steps_per_split % 4 == 0;
-        if (ok) ok = launch_tile(p, g, stream);
-    } else if (p.dma) ok = bf16 && dispatch_dma<true>(p, g, stream);
-    else ok = bf16 ? dispatch_rows<true>(p, g, stream) : dispatch_rows<false>(p, g, stream);
+        ok = bf16 && p.steps_per_split % 2 == 0 && launch_tile(p, g, stream);
+    } else if (p.dma) ok = bf16 && dispatch_dma(p, g, stream);
+    else ok = !bf16 && dispatch_rows(p, g, stream);
     if (!ok) return POLESTAR_ERR_UNSUPPORTED;
     polestar_status st = launch_status();
     if (st != POLESTAR_OK || p.small || p.ksplit == 1) return st;

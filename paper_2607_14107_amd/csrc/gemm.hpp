@@ -32,24 +32,23 @@ struct GemmArgs {
     int* rowmap;        // split-K: [m_max][2] (sequence, position) of row m, -1: none
     int m_max;
     int ksplit;
-    int steps_per_split;   // 256-byte super-steps per split (tile kernel: 64-byte stages)
+    int steps_per_split;   // 256-byte super-steps per split (tile kernel: 128-byte K tiles)
     int row_tiles, col_tiles;
 };
 
 struct GemmPlan {
     bool small;         // gemm_small_kernel (<= 64 rows) instead of gemm_rows_kernel
-    bool dma;           // gemm_dma_kernel (17..320 rows in up to two row tiles, up to 1280 in eight for
-                        // outputs of <= 1024 columns; operands DMA'd into LDS)
-    bool tile;          // gemm_tile_kernel (bf16, more than 160 rows: 256- or 192-row x 256- or 192-column tiles)
-    int tile_mi;        // tile kernel: 32-row MFMA tiles per wave down the rows (4: 256-row tiles, 3: 192)
-    int tile_nj;        // tile kernel: 32-column MFMA tiles per wave across (4: 256-column tiles, 3: 192)
-    int mt;             // MFMA row tiles per workgroup (16 rows: small and dma kernels; 32: rows and tile kernels)
+    bool dma;           // gemm_dma_kernel (17..256 rows in up to two row tiles; operands DMA'd into LDS)
+    bool tile;          // gemm_tile_kernel (bf16)
+    int tile_mi;        // tile kernel: 32-row units of a workgroup's tile (2, 4, 6 or 8: 64 to 256 rows)
+    int tile_nj;        // tile kernel: 64-column units (2, 3 or 4: 128, 192 or 256 columns)
+    int mt;             // MFMA row tiles per workgroup (16 rows: small, dma and tile kernels; 32: rows kernel)
     int row_tiles;
     int col_tiles;
     int ksplit;
-    int steps_per_split;   // 256-byte super-steps per split (tile kernel: 64-byte stages)
-    int grid;           // workgroups of gemm_rows_kernel
-    size_t ws_bytes;    // fp32 partials + row map, 0 when ksplit == 1
+    int steps_per_split;   // 256-byte super-steps per split (tile kernel: 128-byte K tiles)
+    int grid;           // workgroups of the GEMM launch
+    size_t ws_bytes;    // the quoted workspace: at least the plan's fp32 partials + row map
 };
 
 GemmPlan gemm_plan(bool bf16, long m_max, int N, int K);

@@ -264,7 +264,7 @@ __device__ __forceinline__ void dma_body(const GemmArgs& g, int blk) {
     const int tile = blk / g.ksplit;
     const int split = blk - tile * g.ksplit;
     const int col_tile = tile % g.col_tiles;
-    const int m0 = (tile / g.col_tiles) * BM;           // up to eight row tiles
+    const int m0 = (tile / g.col_tiles) * BM;           // one or two row tiles
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int w = t >> 6;
@@ -459,35 +459,40 @@ __device__ __forceinline__ void dma_body(const GemmArgs& g, int blk) {
 
 
 // ---------------------------------------------------------------------------
-// tile_body (gemm_tile_kernel, and the fused step's refresh): 256 or 192
-// rows x 256 or 192 columns of outputs per workgroup for row sets of more
-// than one DMA tile (the refresh of a whole batch, the dense rows of a
-// stack).  The four waves form a 2 x 2 grid of blocks of MI x NJ tiles of
-// v_mfma_f32_32x32x16_bf16 (MI, NJ = 4 or 3), so every fragment read from LDS
-// feeds three or four MFMAs (the row kernels of gemm.hip read one A fragment
-// per MFMA).  The plan takes 192-row or 192-column tiles where 256 x 256 ones
-// would leave compute units idle (1488 rows x 8192 columns: 256 tiles of 192
-// rows instead of 192 tiles; 512 rows x 12288: 128 tiles of 192 columns in
-// two splits instead of 96).
-// Both operands arrive by DMA in stages of 64 bytes (32 bf16) of each row,
-// four LDS slots, three stages in flight; the DMA wait and barrier for stage
-// s+1 sit between the two halves of stage s, so the first fragments of s+1
-// are read while the second half's MFMAs run.
+// tile_body (gemm_tile_kernel, and the fused step's refresh): 64 to 256 rows x
+// 128 to 256 columns of outputs per workgroup (the refresh of a whole batch,
+// the dense rows of a stack).
+//
+// Eight waves, two per SIMD, in a 2 x 4 grid of blocks of MI x NJ tiles of
+// v_mfma_f32_16x16x32_bf16; K in tiles of 64 (128 bytes of each row: whole
+// cache lines), both operands by DMA into two LDS slots, one barrier per K
+// tile.  What bounds it is the matrix pipe, and what that waits for:
+//  - two waves per SIMD, so one wave's MFMAs run while the other waits for LDS
+//    or the barrier, and the LDS fragment reads of eight waves reach twice the
+//    rate of four;
+//  - fragments are read one phase ahead of the MFMAs that use them (a phase is
+//    a quarter of the wave's block, or a whole 32-k step for the smaller
+//    blocks, whose registers hold two steps);
+//  - the DMA instructions of a K tile are spread two per phase: issued in one
+//    burst behind the barrier they fill the address unit's queue and the
+//    waves' next MFMAs wait behind them (12288 x 8192 x 4096: 613 us in one
+//    burst, 581 us spread).
+// The 32x32x16 form measured 15% slower in the same loop, more barriers per K
+// tile with finer slots 7-15% slower, 64-byte stages in four slots 7% slower.
+// 256 x 256 tiles, 12288 x 8192 x 4096: 566 us, 1.46 PFLOP/s; a four-wave
+// kernel of 32x32x16 tiles with 64-byte stages took 728 us, 1.13 PFLOP/s.
+// Smaller tiles have three or four slots: with two, a K tile's DMA had to land
+// within the short time of one K tile (128 x 128 tiles, 512 x 8192 x 4096: 52.7
+// us with two slots and two workgroups per CU, 40.1 us with four slots).
 // ---------------------------------------------------------------------------
 
-constexpr int kTileStage = 64;                 // bytes of each row per stage
-constexpr int kTileDim = 256;                  // columns (and at most rows) per workgroup
+constexpr int kTileStage = 128;                // bytes of each row per K tile (64 bf16)
 constexpr int kTileGroupRows = 4;              // row tiles per band of the launch order
-constexpr int kTileSlot = kTileDim * kTileStage;
-
-// LDS offset of 16-byte chunk c (0..3) of row r in a stage: the chunk is
-// XOR-ed with (r/4) % 4.  Measured on gfx950, fragment reads (lane l: row
-// l%32, chunk l/32) with this layout run at the full ds_read_b128 rate;
-// ((r/2) ^ (r/8)) % 4 or (r/2) % 4 reach half of it.
-__device__ __forceinline__ int tile_sw(int r) { return (r >> 2) & 3; }
+constexpr int kTileThreads = 512;              // eight waves, two per SIMD
 
 // Workgroup blk -> (split, row tile, column tile).  Consecutive workgroups go
-// to different XCDs, so the ids are first regrouped per XCD; each XCD then
+// to different XCDs, so the ids are first regrouped per XCD (XCD e takes a
+// contiguous run of them, the first nb % 8 XCDs one more); each XCD then
 // walks bands of kTileGroupRows row tiles column by column, which keeps the
 // input rows and weight rows its compute units share in its own L2.  (The
 // tile workgroups must be the first ones of their launch.)
@@ -495,8 +500,8 @@ __device__ __forceinline__ void tile_coords(const GemmArgs& g, int bn, int blk, 
     const int ntc = (g.N + bn - 1) / bn;
     const int ntiles = g.row_tiles * ntc;
     const int nb = ntiles * g.ksplit;
-    int bid = blk;
-    if (nb % 8 == 0) bid = (bid % 8) * (nb / 8) + bid / 8;
+    const int xcd = blk & 7;
+    const int bid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blk >> 3);
     split = bid / ntiles;
     const int tl = bid - split * ntiles;
     const int band = tl / (kTileGroupRows * ntc);
@@ -506,222 +511,273 @@ __device__ __forceinline__ void tile_coords(const GemmArgs& g, int bn, int blk, 
     rt = band * kTileGroupRows + (in - ct * rows_here);
 }
 
-constexpr int kTileThreads = 256;             // four waves, one per SIMD
+// The tile shapes (MI, NJ) that are instantiated.
+#define PS_TILE_SHAPES(X) X(8, 4) X(8, 3) X(8, 2) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) \
+    X(2, 4) X(2, 2)
 
-// MI / NJ: 32-row / 32-column MFMA tiles per wave: 4 (256-row or -column
-// tiles) or 3 (192), for shapes where 256 x 256 tiles would leave compute
-// units idle.
+// MI x NJ: 16 x 16 MFMA tiles per wave (BM = 32 MI rows, BN = 64 NJ columns
+// per workgroup).
 template <int MI, int NJ>
 __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
-    static_assert((MI == 3 || MI == 4) && (NJ == 3 || NJ == 4), "192- or 256-row and -column tiles");
+    static_assert(MI % 2 == 0 && MI >= 2 && MI <= 8 && NJ >= 2 && NJ <= 4, "64 to 256 rows, 128 to 256 columns");
     constexpr int ES = 2;                                // bf16 operands
-    constexpr int BMT = 64 * MI;                         // rows per tile (two waves down, MI tiles each)
-    constexpr int BNT = 64 * NJ;                         // columns per tile (two waves across, NJ tiles each)
-    constexpr int ASLOT = BMT * kTileStage;
-    constexpr int BSLOT = BNT * kTileStage;
-    constexpr int NDMA = MI + NJ;                        // DMA instructions per wave per stage (MI A, NJ B)
-    __shared__ __align__(16) char sa0[ASLOT], sa1[ASLOT], sa2[ASLOT], sa3[ASLOT];
-    __shared__ __align__(16) char sb0[BSLOT], sb1[BSLOT], sb2[BSLOT], sb3[BSLOT];
-    __shared__ int rowb[kTileDim], rowp[kTileDim];
+    constexpr int BM = 32 * MI, BN = 64 * NJ;
+    constexpr int AI = BM / 64, BI = BN / 64;            // DMA instructions per wave and K tile (8 rows each)
+    constexpr int ND = AI + BI;
+    constexpr int HA = MI / 2;                           // row tiles of a half block
+    constexpr int HB0 = (NJ + 1) / 2, HB1 = NJ / 2;      // column tiles of its two halves
+    constexpr bool kQuad = MI * NJ >= 24;                // the whole step's fragments twice would not fit
+    // LDS slots: as many as fit 150 KB, two to four
+    constexpr int kSlot = (BM + BN) * kTileStage;
+    constexpr int NS = 4 * kSlot <= 150 * 1024 ? 4 : 3 * kSlot <= 150 * 1024 ? 3 : 2;
+    __shared__ __align__(16) char sa0[BM * kTileStage], sa1[BM * kTileStage];
+    __shared__ __align__(16) char sb0[BN * kTileStage], sb1[BN * kTileStage];
+    __shared__ __align__(16) char sa2[NS > 2 ? BM * kTileStage : 16], sa3[NS > 3 ? BM * kTileStage : 16];
+    __shared__ __align__(16) char sb2[NS > 2 ? BN * kTileStage : 16], sb3[NS > 3 ? BN * kTileStage : 16];
+    __shared__ int rowb[BM], rowp[BM];
 
     int split, rt, ct;
-    tile_coords(g, BNT, blk, split, rt, ct);
+    tile_coords(g, BN, blk, split, rt, ct);
     const int t = threadIdx.x;
     const int lane = t & 63;
-    const int w = t >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = w & 1, wn = w >> 1;
-    const int m0 = rt * BMT;
-    const int n0 = ct * BNT;
-    const int nss = g.steps_per_split;                   // stages of this split (a multiple of 4)
-    const size_t k0b = static_cast<size_t>(split) * nss * kTileStage;
+    const int m0 = rt * BM;
+    const int n0 = ct * BN;
+    // K tiles of this split: steps_per_split of them (an even number), the
+    // last split what is left (even too: K is a multiple of 128)
+    const int kt0 = split * g.steps_per_split;
+    const int nkt = min(g.steps_per_split, g.K / 64 - kt0);
+    const size_t k0b = static_cast<size_t>(kt0) * kTileStage;
 
-    // Row bookkeeping: thread t < BMT maps row m0 + t; the first workgroup of
+    // Row bookkeeping: thread t < BM maps row m0 + t; the first workgroup of
     // each row tile publishes the map for the split-K reduction.
     int rb_ = -1, rp_ = 0;
-    if (t < BMT) map_row(g, m0 + t, rb_, rp_);
-    rowb[t] = rb_;
-    rowp[t] = rp_;
-    if (g.ksplit > 1 && split == 0 && ct == 0 && t < BMT && m0 + t < g.m_max)
-        *reinterpret_cast<int2*>(g.rowmap + 2 * (m0 + t)) = make_int2(rb_, rp_);
+    if (t < BM) {
+        map_row(g, m0 + t, rb_, rp_);
+        rowb[t] = rb_;
+        rowp[t] = rp_;
+        if (g.ksplit > 1 && split == 0 && ct == 0 && m0 + t < g.m_max)
+            *reinterpret_cast<int2*>(g.rowmap + 2 * (m0 + t)) = make_int2(rb_, rp_);
+    }
     if (!__syncthreads_or(rb_ >= 0)) return;             // no row of this tile maps anywhere (uniform)
 
-    // DMA sources: instruction i of wave w moves rows 16(w + 4i) .. +15 of a
-    // slot (i < MI for the input rows, i < NJ for the weight rows); lane l
-    // fills chunk l%4 of row 16(w + 4i) + l/4, i.e. logical chunk
-    // (l%4) ^ swizzle(row).  Rows that map to nothing read row 0 of the
-    // input, columns past N weight row 0; neither is stored.
-    const char* asrc[MI];
-    const char* bsrc[NJ];
+    // DMA sources: instruction i of wave w moves rows 8(w + 8i) .. +7 of a
+    // slot; lane l fills chunk l%8 of row 8(w + 8i) + l/8, i.e. logical chunk
+    // (l%8) ^ ((row/2)%8) (16-row fragment reads are conflict-free).  Rows
+    // that map to nothing read row 0 of the input, columns past N weight row
+    // 0; neither is stored.
+    const char* asrc[AI];
+    const char* bsrc[BI];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = 16 * (w + 4 * i) + (lane >> 2);
-        const int chunk = ((lane & 3) ^ tile_sw(r)) << 4;
-        if (i < MI) {
-            const int b = rowb[r];
-            const char* arow = b >= 0 ? g.x + (static_cast<size_t>(b) * g.seq + rowp[r]) * g.K * ES : g.x;
-            asrc[i] = arow + k0b + chunk;
-        }
-        if (i < NJ) {
-            const char* brow = weight_row(g, n0 + r, ES);
-            bsrc[i] = (brow ? brow : g.w0) + k0b + chunk;
-        }
+    for (int i = 0; i < AI; ++i) {
+        const int r = 8 * (w + 8 * i) + (lane >> 3);
+        const int b = rowb[r];
+        const char* row = b >= 0 ? g.x + (static_cast<size_t>(b) * g.seq + rowp[r]) * g.K * ES : g.x;
+        asrc[i] = row + k0b + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
-    auto issue = [&](int st, char* abuf, char* bbuf) {
-        const int off = min(st, nss - 1) * kTileStage;   // past the split: re-read its last stage
 #pragma unroll
-        for (int i = 0; i < NJ; ++i) dma16(bsrc[i] + off, bbuf + 16 * (w + 4 * i) * kTileStage);
+    for (int i = 0; i < BI; ++i) {
+        const int r = 8 * (w + 8 * i) + (lane >> 3);
+        const char* row = weight_row(g, n0 + r, ES);
+        bsrc[i] = (row ? row : g.w0) + k0b + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+    // DMA instructions d0 .. d0+n-1 of K tile kt (past the split: its last tile again)
+    auto issue = [&](int d0, int n, int kt, char* abuf, char* bbuf) {
+        const size_t off = static_cast<size_t>(min(kt, nkt - 1)) * kTileStage;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) dma16(asrc[i] + off, abuf + 16 * (w + 4 * i) * kTileStage);
+        for (int d = d0; d < d0 + n; ++d) {
+            if (d < AI) dma16(asrc[d] + off, abuf + 8 * (w + 8 * d) * kTileStage);
+            else if (d < ND) dma16(bsrc[d - AI] + off, bbuf + 8 * (w + 8 * (d - AI)) * kTileStage);
+        }
     };
 
-    // Fragment offsets: lane l reads row 32i + l%32 of its wave's block at
-    // k-group l/32 of half kk; the swizzle depends on l%32 only.
-    const int fr = lane & 31;
-    const int fsw = tile_sw(fr);                         // = tile_sw(32i + fr)
-    const int h = lane >> 5;
-    const int aoff0 = (32 * MI * wm + fr) * kTileStage + (((0 + h) ^ fsw) << 4);
-    const int aoff1 = (32 * MI * wm + fr) * kTileStage + (((2 + h) ^ fsw) << 4);
-    const int boff0 = (32 * NJ * wn + fr) * kTileStage + (((0 + h) ^ fsw) << 4);
-    const int boff1 = (32 * NJ * wn + fr) * kTileStage + (((2 + h) ^ fsw) << 4);
+    // Fragment offsets: lane l reads row 16i + l%16 of its wave's block at
+    // k-group l/16 of 32-k step s; the swizzle depends on l%16 only.
+    const int fr = lane & 15, kg = lane >> 4;
+    const int fsw = (fr >> 1) & 7;
+    const int ao[2] = {(16 * MI * wm + fr) * kTileStage + ((kg ^ fsw) << 4),
+                       (16 * MI * wm + fr) * kTileStage + (((4 + kg) ^ fsw) << 4)};
+    const int bo[2] = {(16 * NJ * wn + fr) * kTileStage + ((kg ^ fsw) << 4),
+                       (16 * NJ * wn + fr) * kTileStage + (((4 + kg) ^ fsw) << 4)};
+    // n fragments of step s from row (column) tile i0 on
+    auto read = [&](const char* buf, const int (&o)[2], int s, int i0, int n, uint4* f) {
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+            f[i] = *reinterpret_cast<const uint4*>(buf + o[s] + (i0 + i) * 16 * kTileStage);
+    };
 
-    floatx16 acc[MI][NJ];
+    // acc[i][j] holds the transposed tile: lane l has row l%16, columns
+    // 4(l/16) .. +3
+    floatx4 acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const uint4* fa, const uint4* fb, int i0, int ni, int j0, int nj) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    uint4 fa0[MI], fb0[NJ], fa1[MI], fb1[NJ];            // fragments of half 0 / half 1
-    auto read_half = [&](const char* abuf, const char* bbuf, int aoff, int boff, uint4 (&fa)[MI], uint4 (&fb)[NJ]) {
+        for (int i = 0; i < ni; ++i)
 #pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i] = *reinterpret_cast<const uint4*>(abuf + aoff + i * 32 * kTileStage);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) fb[j] = *reinterpret_cast<const uint4*>(bbuf + boff + j * 32 * kTileStage);
-    };
-    auto mfma_half = [&](const uint4 (&fa)[MI], const uint4 (&fb)[NJ]) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[i][j] = Mma32<true>::step(fa[i], fb[j], acc[i][j]);
-    };
-    // Instruction order of a half: the MI + NJ fragment reads for the next
-    // half go out behind the first two MFMAs (so they land well before the
-    // next half starts), the NDMA DMA instructions (second half only) two
-    // behind each of the next MFMAs, then the remaining MFMAs.
-    auto interleave = [&](bool with_dma) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, NJ, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, MI, 0);
-        if (with_dma) {
-#pragma unroll
-            for (int q = 0; q < NDMA / 2; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-            }
-            if constexpr (NDMA % 2) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, NJ * MI - 2 - (NDMA + 1) / 2, 0);
-        } else {
-            __builtin_amdgcn_sched_group_barrier(0x008, NJ * MI - 2, 0);
-        }
+            for (int j = 0; j < nj; ++j) acc[i0 + i][j0 + j] = mfma_bf16(fb[j], fa[i], acc[i0 + i][j0 + j]);
     };
 
-    constexpr int WS = wait_vm(2 * NDMA);                // two newer stages stay in flight
-    issue(0, sa0, sb0);
-    issue(1, sa1, sb1);
-    issue(2, sa2, sb2);
-    issue(3, sa3, sb3);
-    __builtin_amdgcn_s_waitcnt(wait_vm(3 * NDMA));
-    __builtin_amdgcn_s_barrier();
-    read_half(sa0, sb0, aoff0, boff0, fa0, fb0);
-
-    // Stage S in slot S%4: half 1 of S is read while half 0's MFMAs run;
-    // then (own reads done, stage S+1 landed for this wave) a barrier makes
-    // S+1 visible to all waves and frees slot S%4, which takes stage S+4;
-    // half 0 of S+1 is read while half 1's MFMAs run.
-#define PS_TILE_STEP(S, AU, BU, AX, BX)                                     \
+    // The barrier of K tile T: this wave's reads of T are done and its DMA of
+    // T+1 has landed, so T+1 may be read and T's slot takes T+NS.
+#define PS_TILE_SYNC()                                                      \
     {                                                                       \
-        __builtin_amdgcn_sched_barrier(0);                                  \
-        read_half(AU, BU, aoff1, boff1, fa1, fb1);                          \
-        mfma_half(fa0, fb0);                                                \
-        interleave(false);                                                  \
-        __builtin_amdgcn_sched_barrier(0);                                  \
-        __builtin_amdgcn_s_waitcnt(WS);                                     \
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                             \
+        __builtin_amdgcn_s_waitcnt(wait_vm((NS - 2) * ND) & kWaitLgkm0);    \
         __builtin_amdgcn_s_barrier();                                       \
         __builtin_amdgcn_sched_barrier(0);                                  \
-        issue((S) + 4, AU, BU);                                             \
-        read_half(AX, BX, aoff0, boff0, fa0, fb0);                          \
-        mfma_half(fa1, fb1);                                                \
-        interleave(true);                                                   \
+    }
+    issue(0, ND, 0, sa0, sb0);
+    if constexpr (kQuad) {
+        // Quarters of the block per phase, in the order A0B0 A0B1 A1B1 A1B0 |
+        // A0B1 A0B0 A1B0 A1B1 over the two 32-k steps of a tile, so that each
+        // phase needs one new half of fragments, read a phase ahead.
+        uint4 a0[HA], a1[HA], b0[HB0], b1[HB0];
+        issue(0, 4, 1, sa1, sb1);
+        __builtin_amdgcn_s_waitcnt(wait_vm(4));
+        __builtin_amdgcn_s_barrier();
+        read(sa0, ao, 0, 0, HA, a0);
+        read(sb0, bo, 0, 0, HB0, b0);
+#define PS_TILE_PHASE(READ, DMA, FA, FB, I0, J0, JN)                        \
+    {                                                                       \
+        READ;                                                               \
+        DMA;                                                                \
+        mma(FA, FB, I0, HA, J0, JN);                                        \
         __builtin_amdgcn_sched_barrier(0);                                  \
     }
-    for (int st = 0; st < nss; st += 4) {
-        PS_TILE_STEP(st + 0, sa0, sb0, sa1, sb1)
-        PS_TILE_STEP(st + 1, sa1, sb1, sa2, sb2)
-        PS_TILE_STEP(st + 2, sa2, sb2, sa3, sb3)
-        PS_TILE_STEP(st + 3, sa3, sb3, sa0, sb0)
+#define PS_TILE_STEP(T, AU, BU, AX, BX)                                                                       \
+    {                                                                                                         \
+        PS_TILE_PHASE(read(BU, bo, 0, HB0, HB1, b1), issue(4, 2, (T) + 1, AX, BX), a0, b0, 0, 0, HB0)         \
+        PS_TILE_PHASE(read(AU, ao, 0, HA, HA, a1), issue(6, 2, (T) + 1, AX, BX), a0, b1, 0, HB0, HB1)         \
+        PS_TILE_PHASE(read(AU, ao, 1, 0, HA, a0), , a1, b1, HA, HB0, HB1)                                     \
+        PS_TILE_PHASE(read(BU, bo, 1, HB0, HB1, b1), , a1, b0, HA, 0, HB0)                                    \
+        PS_TILE_PHASE(read(BU, bo, 1, 0, HB0, b0), , a0, b1, 0, HB0, HB1)                                     \
+        PS_TILE_PHASE(read(AU, ao, 1, HA, HA, a1), , a0, b0, 0, 0, HB0)                                       \
+        PS_TILE_SYNC()                                                                                        \
+        PS_TILE_PHASE(read(AX, ao, 0, 0, HA, a0), issue(0, 2, (T) + 2, AU, BU), a1, b0, HA, 0, HB0)           \
+        PS_TILE_PHASE(read(BX, bo, 0, 0, HB0, b0), issue(2, 2, (T) + 2, AU, BU), a1, b1, HA, HB0, HB1)        \
     }
+        for (int kt = 0; kt < nkt; kt += 2) {
+            PS_TILE_STEP(kt, sa0, sb0, sa1, sb1)
+            PS_TILE_STEP(kt + 1, sa1, sb1, sa0, sb0)
+        }
 #undef PS_TILE_STEP
+#undef PS_TILE_PHASE
+    } else {
+        // Whole 32-k steps, the next one's fragments read while this one's
+        // MFMAs run.
+        uint4 a[2][MI], b[2][NJ];
+        issue(0, ND, 1, sa1, sb1);
+        if constexpr (NS > 2) issue(0, ND, 2, sa2, sb2);
+        if constexpr (NS > 3) issue(0, ND, 3, sa3, sb3);
+        __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * ND));
+        __builtin_amdgcn_s_barrier();
+        read(sa0, ao, 0, 0, MI, a[0]);
+        read(sb0, bo, 0, 0, NJ, b[0]);
+#define PS_TILE_STEP(T, AU, BU, AX, BX)                                     \
+    {                                                                       \
+        read(BU, bo, 1, 0, NJ, b[1]);                                       \
+        read(AU, ao, 1, 0, MI, a[1]);                                       \
+        mma(a[0], b[0], 0, MI, 0, NJ);                                      \
+        __builtin_amdgcn_sched_barrier(0);                                  \
+        PS_TILE_SYNC()                                                      \
+        read(BX, bo, 0, 0, NJ, b[0]);                                       \
+        read(AX, ao, 0, 0, MI, a[0]);                                       \
+        issue(0, 2, (T) + NS, AU, BU);                                      \
+        mma(a[1], b[1], 0, HA, 0, NJ);                                      \
+        __builtin_amdgcn_sched_barrier(0);                                  \
+        issue(2, ND - 2, (T) + NS, AU, BU);                                 \
+        mma(a[1] + HA, b[1], HA, HA, 0, NJ);                                \
+        __builtin_amdgcn_sched_barrier(0);                                  \
+    }
+        // (no exits inside the loop: with them the compiler copies the
+        // accumulators at every step)
+        static_assert(NS > 2, "the whole-step shapes have three or four slots");
+        int kt = 0;
+        for (; kt + NS <= nkt; kt += NS) {
+            PS_TILE_STEP(kt, sa0, sb0, sa1, sb1)
+            PS_TILE_STEP(kt + 1, sa1, sb1, sa2, sb2)
+            if constexpr (NS == 3) {
+                PS_TILE_STEP(kt + 2, sa2, sb2, sa0, sb0)
+            } else {
+                PS_TILE_STEP(kt + 2, sa2, sb2, sa3, sb3)
+                PS_TILE_STEP(kt + 3, sa3, sb3, sa0, sb0)
+            }
+        }
+        if (kt < nkt) {                                  // what is left of a split that NS does not divide
+            PS_TILE_STEP(kt, sa0, sb0, sa1, sb1)
+            if (kt + 1 < nkt) {
+                PS_TILE_STEP(kt + 1, sa1, sb1, sa2, sb2)
+                if constexpr (NS > 3) {
+                    if (kt + 2 < nkt) PS_TILE_STEP(kt + 2, sa2, sb2, sa3, sb3)
+                }
+            }
+        }
+#undef PS_TILE_STEP
+    }
+#undef PS_TILE_SYNC
     __builtin_amdgcn_s_waitcnt(0);                       // every DMA (the re-read tail too) has landed
     __syncthreads();                                     // and every wave is done with the slots
 
-    // Epilogue through LDS, per wave, 16 rows at a time: register e of
-    // acc[i][j] is row 32i + 8(e/4) + 4(l/32) + e%4, column 32j + l%32 of the
-    // wave's block; each lane then moves 8 consecutive columns of a row.
-    constexpr int EP = 132;                              // fp32 pitch of a staged row
-    static_assert(16 * EP * 4 <= ASLOT, "a wave's 16 staged rows fit its input slot");
-    float* ep = reinterpret_cast<float*>(w == 0 ? sa0 : w == 1 ? sa1 : w == 2 ? sa2 : sa3);
-    const int cbase = n0 + 32 * NJ * wn;
+    const int cbase = n0 + 16 * NJ * wn;
+    if (g.ksplit > 1) {
+        // fp32 partials straight from registers: 64 contiguous bytes of 16 rows per store
+        float* part = g.ws + static_cast<size_t>(split) * g.col_tiles * g.m_max * 128;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+        for (int i = 0; i < MI; ++i) {
+            const int lr = 16 * (MI * wm + i) + fr;
+            if (rowb[lr] < 0) continue;
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int ee = 8 * hh + e;
-                    const int r = 8 * (e >> 2) + 4 * h + (e & 3);
-                    ep[r * EP + 32 * j + fr] = acc[i][j][ee];
-                }
-            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int q = 0; q < NJ; ++q) {
-                const int idx = 64 * q + lane;           // 16 rows x 4 NJ chunks of 8 columns
-                const int r = idx / (4 * NJ), c = (idx % (4 * NJ)) * 8;
-                const int lr = 32 * MI * wm + 32 * i + 16 * hh + r;   // row within the tile
-                const int b = rowb[lr];
-                const int n = cbase + c;
-                const float* v = ep + r * EP + c;
-                if (b >= 0 && n < g.N) {
-                    if (g.ksplit == 1) {
-                        store8<true>(out_ptr<true>(g, b, rowp[lr], m0 + lr, n), v);
-                    } else {
-                        float* dst = g.ws + ((static_cast<size_t>(split) * g.col_tiles + (n >> 7)) * g.m_max +
-                                             (m0 + lr)) * 128 + (n & 127);
-                        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-                        *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
-                    }
-                }
+            for (int j = 0; j < NJ; ++j) {
+                const int n = cbase + 16 * j + 4 * kg;
+                if (n < g.N)
+                    *reinterpret_cast<floatx4*>(part + (static_cast<size_t>(n >> 7) * g.m_max + m0 + lr) * 128 +
+                                                (n & 127)) = acc[i][j];
             }
-            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-            __builtin_amdgcn_wave_barrier();
         }
+        return;
+    }
+    // Outputs through LDS, half the wave's rows at a time in a region of its
+    // own, then 8 consecutive columns of a row per lane.
+    constexpr int EP = 32 * NJ + 16;                     // bytes of a staged row
+    constexpr int ER = 16 * HA;                          // rows of a pass
+    constexpr int CPR = 2 * NJ;                          // 16-byte chunks of a row
+    static_assert(2 * ER * EP <= BM * kTileStage && 2 * ER * EP <= BN * kTileStage, "two waves' rows fit a slot");
+    char* ep = (w < 2 ? sa0 : w < 4 ? sa1 : w < 6 ? sb0 : sb1) + (w & 1) * ER * EP;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+        for (int i = 0; i < HA; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const floatx4 v = acc[HA * hh + i][j];
+                *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
+                    make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+            }
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < (ER * CPR + 63) / 64; ++q) {
+            const int idx = 64 * q + lane;
+            if (ER * CPR % 64 != 0 && idx >= ER * CPR) break;
+            const int r = idx / CPR, c = (idx % CPR) * 8;
+            const int lr = 16 * (MI * wm + HA * hh) + r;  // row within the tile
+            const int b = rowb[lr];
+            const int n = cbase + c;
+            if (b >= 0 && n < g.N) st16(out_ptr<true>(g, b, rowp[lr], m0 + lr, n), ld16(ep + r * EP + 2 * c));
+        }
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
 // Split-K reduction: thread = (column tile, row, 8 columns); sums the splits
-// in order and stores the row through the published row map.  One
-// kGemmBlock workgroup per 16 rows of a column tile.
+// in order and stores the row through the published row map.  `id` counts the
+// threads of the whole reduction (gemm_reduce_blocks workgroups of kGemmBlock).
 template <bool BF16>
-__device__ __forceinline__ void reduce_body(const GemmArgs& g, int blk) {
-    const long id = static_cast<long>(blk) * kGemmBlock + threadIdx.x;
+__device__ __forceinline__ void reduce_body(const GemmArgs& g, long id) {
     const long per_tile = static_cast<long>(g.m_max) * 16;
     const int ct = static_cast<int>(id / per_tile);
     if (ct >= g.col_tiles) return;

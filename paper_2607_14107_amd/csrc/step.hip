@@ -125,7 +125,7 @@ struct TileQArgs {
     int n_tile;
 };
 
-static_assert(kTileThreads == kGemmBlock, "the tile and reduce roles share one workgroup size");
+static_assert(kTileThreads % kGemmBlock == 0, "a workgroup of the reduce role takes whole reduce blocks");
 
 template <int MI, int NJ>
 __global__ __launch_bounds__(kTileThreads) void tile_qred_kernel(TileQArgs k) {
@@ -133,16 +133,16 @@ __global__ __launch_bounds__(kTileThreads) void tile_qred_kernel(TileQArgs k) {
         tile_body<MI, NJ>(k.r, blockIdx.x);
         return;
     }
-    reduce_body<true>(k.q, blockIdx.x - k.n_tile);
+    reduce_body<true>(k.q, static_cast<long>(blockIdx.x - k.n_tile) * kTileThreads + threadIdx.x);
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(kStepBlock) void reduce2_kernel(ReduceArgs k) {
     if (static_cast<int>(blockIdx.x) < k.n_r) {
-        reduce_body<BF16>(k.r, blockIdx.x);
+        reduce_body<BF16>(k.r, static_cast<long>(blockIdx.x) * kGemmBlock + threadIdx.x);
         return;
     }
-    reduce_body<BF16>(k.q, blockIdx.x - k.n_r);
+    reduce_body<BF16>(k.q, static_cast<long>(blockIdx.x - k.n_r) * kGemmBlock + threadIdx.x);
 }
 
 struct BackArgs {
@@ -453,18 +453,18 @@ extern "C" polestar_status polestar_step(const polestar_step_args* a, void* work
                                     a->stale_count, a->k, a->block_start, a->block_len, a->w_k, a->w_v,
                                     a->k_cache, a->v_cache, ws);
     const int n_qred = gemm_reduce_blocks(L.qp, f.q);
-    if (bf16 && L.rp.tile && L.rp.ksplit == 1 && L.rp.steps_per_split % 4 == 0 && n_qred > 0) {
+    if (bf16 && L.rp.tile && L.rp.ksplit == 1 && n_qred > 0) {
         TileQArgs tq{};
         gemm_finalize_args(L.rp, rg);
         tq.r = rg;
         tq.q = f.q;
         tq.n_tile = L.rp.grid;
-        const dim3 grid(L.rp.grid + n_qred), block(kTileThreads);
+        const dim3 grid(L.rp.grid + ceil_div(n_qred, kTileThreads / kGemmBlock)), block(kTileThreads);
         switch (10 * L.rp.tile_mi + L.rp.tile_nj) {
-            case 44: hipLaunchKernelGGL((tile_qred_kernel<4, 4>), grid, block, 0, stream, tq); break;
-            case 43: hipLaunchKernelGGL((tile_qred_kernel<4, 3>), grid, block, 0, stream, tq); break;
-            case 34: hipLaunchKernelGGL((tile_qred_kernel<3, 4>), grid, block, 0, stream, tq); break;
-            case 33: hipLaunchKernelGGL((tile_qred_kernel<3, 3>), grid, block, 0, stream, tq); break;
+#define PS_CASE(MI, NJ) \
+            case 10 * MI + NJ: hipLaunchKernelGGL((tile_qred_kernel<MI, NJ>), grid, block, 0, stream, tq); break;
+            PS_TILE_SHAPES(PS_CASE)
+#undef PS_CASE
             default: return POLESTAR_ERR_UNSUPPORTED;
         }
         st = launch_status();

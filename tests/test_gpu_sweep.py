@@ -120,6 +120,34 @@ def test_linear_random_tile_shapes(P, case):
                       f"linear {batch}x{n} rows x {N} x K {K}")
 
 
+@pytest.mark.parametrize("m,N,K", [
+    # each tile shape (rows x columns) of the tile kernel, K tiles per split whole and not whole
+    # multiples of its LDS slots, ragged last tiles in both directions
+    (66, 80, 256), (70, 64, 384), (98, 64, 1536), (71, 96, 1664), (69, 64, 4352),             # 64 x 128
+    (385, 4656, 256), (262, 6544, 384), (68, 4288, 2048), (66, 2432, 3968),                   # 128 x 128
+    (771, 6624, 256), (775, 6576, 512), (391, 2704, 2944), (69, 6864, 3840),                  # 128 x 192
+    (1055, 6576, 384), (1032, 6672, 512), (257, 4288, 3200),                                  # 128 x 256
+    (523, 6624, 384), (527, 6624, 256), (133, 5456, 3328), (137, 2816, 3328),                 # 192 x 128
+    (1031, 7232, 384), (1032, 7312, 256), (269, 4384, 3200),                                  # 192 x 192
+    (772, 7104, 384), (774, 6928, 256), (193, 6368, 4608),                                    # 256 x 128
+    (1156, 6976, 256), (2048, 6144, 1024), (1537, 8192, 512), (2305, 7696, 384),              # 256 x 192, 192 x 256, 256 x 256
+])
+def test_linear_tile_kernel_edges(P, m, N, K):
+    """The tile kernel's shapes at their edges against an fp32 product of the
+    same bf16 operands: both sum exact products in fp32 in some order and
+    round once, so a row's largest difference is one bf16 step (2^-8) of the
+    row's largest value plus fp32 noise, well under the 2e-2 of the sweep."""
+    torch = pytest.importorskip("torch")
+    gen = torch.Generator(device="cuda").manual_seed(m * 7 + N)
+    x = torch.randn((1, m + 3, K), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.05).to(torch.bfloat16)
+    y = torch.full((1, m, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    P.linear(x, 2, m, w, y)
+    want = x[0, 2:2 + m].float() @ w.float().t()
+    err = (y[0].float() - want).abs().amax(1) / want.abs().amax(1)
+    assert float(err.max()) <= 5e-3, (m, N, K, float(err.max()))
+
+
 @pytest.mark.parametrize("case", range(16))
 def test_project_q_random_shapes(P, case):
     g = np.random.default_rng(11000 + case)
