@@ -645,6 +645,33 @@ polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t s
     return launch_status();
 }
 
+// Estimated time of a tile plan for m rows.
+static double plan_cost(const GemmPlan& p, long m, int N) {
+    const long tiles = static_cast<long>(ceil_div(m, 32 * p.tile_mi)) * ceil_div(N, 64 * p.tile_nj);
+    return tile_cost(p.tile_mi, p.tile_nj, tiles, p.ksplit, p.steps_per_split, m, N);
+}
+
+// Half the capacity is the line because a packet holds the members of half the
+// clusters (16 lists of 96 entries, 47 used, 8192 x 4096: unpacked 82 us,
+// packed in the plan of 768 rows and the other plan's empty launch 57 us);
+// a launch that returns at once takes 4.5 us, priced at 4.
+polestar_status gemm_run_refresh(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t stream) {
+    if (!bf16 || !p.tile || p.ksplit > 1 || g.block_len > 0 || g.k_max == 0 || g.batch > kMaxPacked)
+        return gemm_run(bf16, p, g, stream);
+    const int half = ceil_div(g.m_max, 2);
+    const GemmPlan q = gemm_plan(bf16, half, g.N, g.K);
+    if (!q.tile || q.ksplit > 1 || plan_cost(q, half, g.N) + 4.0 > plan_cost(p, g.m_max, g.N))
+        return gemm_run(bf16, p, g, stream);
+    g.packed = 1;
+    g.rows_lo = 0;
+    g.rows_hi = half;
+    const polestar_status st = gemm_run(bf16, q, g, stream);
+    if (st != POLESTAR_OK) return st;
+    g.rows_lo = half;
+    g.rows_hi = g.m_max;
+    return gemm_run(bf16, p, g, stream);
+}
+
 }  // namespace ps
 
 extern "C" size_t polestar_refresh_kv_workspace_size(polestar_dtype dtype, int batch, int d,
@@ -687,7 +714,7 @@ extern "C" polestar_status polestar_refresh_kv(polestar_dtype dtype, int batch, 
     if (workspace_bytes < p.ws_bytes || (p.ws_bytes > 0 && !workspace)) return POLESTAR_ERR_WORKSPACE;
     const GemmArgs g = refresh_gemm_args(batch, seq, d, kvd, h_cur, stale_idx, stale_count, k_max, block_start,
                                          block_len, w_k, w_v, k_cache, v_cache, workspace);
-    return gemm_run(bf16, p, g, stream);
+    return gemm_run_refresh(bf16, p, g, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -774,5 +801,5 @@ extern "C" polestar_status polestar_refresh_kv_noalloc(polestar_dtype dtype, int
     }
     const GemmArgs g = refresh_gemm_args(batch, seq, d, kvd, h_cur, stale_idx, stale_count, k_max, block_start,
                                          block_len, w_k, w_v, k_cache, v_cache, ws);
-    return gemm_run(bf16, p, g, stream);
+    return gemm_run_refresh(bf16, p, g, stream);
 }

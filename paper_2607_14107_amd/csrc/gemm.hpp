@@ -34,7 +34,13 @@ struct GemmArgs {
     int ksplit;
     int steps_per_split;   // 256-byte super-steps per split (tile kernel: 128-byte K tiles)
     int row_tiles, col_tiles;
+    // Packed rows (refresh mode without a block, batch <= kMaxPacked, tile
+    // kernel, unsplit): the lists' used entries alone, one sequence after the
+    // other, and the launch returns unless rows_lo < their number <= rows_hi.
+    int packed, rows_lo, rows_hi;
 };
+
+constexpr int kMaxPacked = 256;   // sequences whose counts a workgroup scans
 
 struct GemmPlan {
     bool small;         // gemm_small_kernel (<= 64 rows) instead of gemm_rows_kernel
@@ -63,6 +69,11 @@ inline bool gemm_k_ok(bool bf16, int K) { return K > 0 && K % (bf16 ? 128 : 64) 
 // POLESTAR_OK or a launch error.
 polestar_status gemm_run(bool bf16, const GemmPlan& plan, GemmArgs g, hipStream_t stream,
                          GemmArgs* deferred = nullptr);
+
+// gemm_run of a refresh (refresh_gemm_args).  Lists without a block are update
+// packets, sized for the whole window and usually about half full: their used
+// rows are packed, and the plan for half the capacity runs where they fit it.
+polestar_status gemm_run_refresh(bool bf16, const GemmPlan& plan, GemmArgs g, hipStream_t stream);
 
 // Arguments of the K/V refresh GEMM (polestar_refresh_kv's, after its checks):
 // rows = the stale positions and the active block of every sequence, output

@@ -496,19 +496,53 @@ constexpr int kTileThreads = 512;              // eight waves, two per SIMD
 // walks bands of kTileGroupRows row tiles column by column, which keeps the
 // input rows and weight rows its compute units share in its own L2.  (The
 // tile workgroups must be the first ones of their launch.)
-__device__ __forceinline__ void tile_coords(const GemmArgs& g, int bn, int blk, int& split, int& rt, int& ct) {
+// False for a workgroup past the last tile (fewer row tiles than launched for).
+__device__ __forceinline__ bool tile_coords(const GemmArgs& g, int row_tiles, int bn, int blk, int& split, int& rt,
+                                            int& ct) {
     const int ntc = (g.N + bn - 1) / bn;
-    const int ntiles = g.row_tiles * ntc;
+    const int ntiles = row_tiles * ntc;
     const int nb = ntiles * g.ksplit;
+    if (blk >= nb) return false;
     const int xcd = blk & 7;
     const int bid = xcd * (nb >> 3) + min(xcd, nb & 7) + (blk >> 3);
     split = bid / ntiles;
     const int tl = bid - split * ntiles;
     const int band = tl / (kTileGroupRows * ntc);
-    const int rows_here = min(kTileGroupRows, g.row_tiles - band * kTileGroupRows);
+    const int rows_here = min(kTileGroupRows, row_tiles - band * kTileGroupRows);
     const int in = tl - band * kTileGroupRows * ntc;
     ct = in / rows_here;
     rt = band * kTileGroupRows + (in - ct * rows_here);
+    return true;
+}
+
+// Packed rows: the running sum of the lists' counts (first[b] rows come before
+// sequence b's, first[batch] in all).  All kTileThreads threads.
+__device__ __forceinline__ void packed_rows(const GemmArgs& g, int* first) {
+    __shared__ int scratch[17];
+    const int t = threadIdx.x;
+    const int c = t < g.batch ? min(max(g.stale_count[t], 0), g.k_max) : 0;
+    int total;
+    const int before = block_excl_scan(c, scratch, &total);
+    if (t <= kMaxPacked) first[t] = before;              // batch <= kMaxPacked
+    __syncthreads();
+}
+
+// Packed row m -> (sequence, position); b = -1 past the last row and for
+// entries outside the sequence.
+__device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, int m, int& b, int& pos) {
+    b = -1;
+    pos = 0;
+    if (m >= first[g.batch]) return;
+    int lo = 0, hi = g.batch;                            // first[lo] <= m < first[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (first[mid] <= m) lo = mid;
+        else hi = mid;
+    }
+    const int p = g.stale_idx[static_cast<size_t>(lo) * g.k_max + (m - first[lo])];
+    if (p < 0 || p >= g.seq) return;
+    b = lo;
+    pos = p;
 }
 
 // The tile shapes (MI, NJ) that are instantiated.
@@ -535,10 +569,18 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
     __shared__ __align__(16) char sa2[NS > 2 ? BM * kTileStage : 16], sa3[NS > 3 ? BM * kTileStage : 16];
     __shared__ __align__(16) char sb2[NS > 2 ? BN * kTileStage : 16], sb3[NS > 3 ? BN * kTileStage : 16];
     __shared__ int rowb[BM], rowp[BM];
+    __shared__ int first[kMaxPacked + 1];
 
-    int split, rt, ct;
-    tile_coords(g, BN, blk, split, rt, ct);
     const int t = threadIdx.x;
+    int row_tiles = g.row_tiles;
+    if (g.packed) {
+        packed_rows(g, first);
+        const int total = first[g.batch];
+        if (total <= g.rows_lo || total > g.rows_hi) return;   // (uniform)
+        row_tiles = (total + BM - 1) / BM;
+    }
+    int split, rt, ct;
+    if (!tile_coords(g, row_tiles, BN, blk, split, rt, ct)) return;
     const int lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = w & 1, wn = w >> 1;
@@ -554,7 +596,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
     // each row tile publishes the map for the split-K reduction.
     int rb_ = -1, rp_ = 0;
     if (t < BM) {
-        map_row(g, m0 + t, rb_, rp_);
+        if (g.packed) map_packed(g, first, m0 + t, rb_, rp_);
+        else map_row(g, m0 + t, rb_, rp_);
         rowb[t] = rb_;
         rowp[t] = rp_;
         if (g.ksplit > 1 && split == 0 && ct == 0 && m0 + t < g.m_max)

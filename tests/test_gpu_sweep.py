@@ -241,3 +241,49 @@ def test_refresh_narrow_output_many_row_tiles(P, batch, seq, bs, bl, d, kvh, hd,
         vw = ref.project_rows(hdec[b], wvd, rows).reshape(rows.size, kvh, hd)
         assert_rows_close(ref.decode(kg[b, rows], dtype), kw, RTOL[dtype], f"K rows b{b}")
         assert_rows_close(ref.decode(vg[b, rows], dtype), vw, RTOL[dtype], f"V rows b{b}")
+
+
+@pytest.mark.parametrize("batch,k_max,counts", [
+    (3, 500, "half"), (3, 500, "exactly half"), (3, 500, "one more"), (3, 500, "full"), (3, 500, "none"),
+    (16, 96, "half"), (16, 96, "uneven"),
+])
+def test_refresh_packed_lists(P, batch, k_max, counts):
+    """Lists without a block that are not full: their used rows are packed and
+    run in the plan for half the capacity when they fit it, in the other one
+    when not.  Entries outside the sequence are skipped, rows no entry names
+    stay byte-identical, the rest are within a bf16 step of an fp32 product."""
+    torch = pytest.importorskip("torch")
+    d, kvh, hd, seq = 512, 32, 128, k_max + 37
+    g = np.random.default_rng(batch + k_max)
+    half = (batch * k_max + 1) // 2
+    cnt = np.zeros(batch, dtype=np.int64)
+    if counts == "half":
+        cnt[:] = int(0.45 * k_max)
+    elif counts == "full":
+        cnt[:] = k_max
+    elif counts == "uneven":
+        cnt[:] = g.integers(0, k_max, size=batch)
+        cnt[3], cnt[7] = 0, k_max
+    elif counts != "none":
+        left = half + (counts == "one more")
+        for b in range(batch):
+            cnt[b] = min(k_max, left)
+            left -= cnt[b]
+    idx = np.stack([g.permutation(seq)[:k_max] for _ in range(batch)]).astype(np.int32)
+    idx[0, 5], idx[1, 0], idx[2, 7] = -1, seq, -7
+    gen = torch.Generator(device="cuda").manual_seed(k_max)
+    rnd = lambda *sh: torch.randn(sh, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    h, wk, wv = rnd(batch, seq, d), rnd(kvh * hd, d) * 0.05, rnd(kvh * hd, d) * 0.05
+    kc0, vc0 = rnd(batch, seq, kvh, hd), rnd(batch, seq, kvh, hd)
+    kc, vc = kc0.clone(), vc0.clone()
+    P.refresh_kv(h, _i32(idx), _i32(cnt), 0, 0, wk, wv, kc, vc)
+    for b in range(batch):
+        rows = [int(p) for p in idx[b, :cnt[b]] if 0 <= p < seq]
+        keep = torch.ones(seq, dtype=torch.bool, device="cuda")
+        keep[rows] = False
+        for got, was, w in ((kc, kc0, wk), (vc, vc0, wv)):
+            assert torch.equal(got[b][keep], was[b][keep]), (b, counts)
+            if rows:
+                want = h[b, rows].float() @ w.float().t()
+                err = (got[b, rows].reshape(len(rows), -1).float() - want).abs().amax(1) / want.abs().amax(1)
+                assert float(err.max()) <= 5e-3, (b, counts, float(err.max()))
