@@ -438,3 +438,59 @@ def test_attention_drift_matches_oracle(P, dtype, b, seq, R, H, Hkv, hd):
     # an unchanged cache gives (numerically) zero drift
     d2 = P.attention_drift(qt, to_dev(k1, dtype), scores, lse, False)
     assert np.abs(from_dev(d2)).max() < 1e-5
+
+
+@pytest.mark.parametrize("dtype,d,shift", [("bf16", 264, 0), ("bf16", 260, 1), ("fp32", 1028, 0), ("fp32", 260, 1)])
+def test_cluster_update_long_lists_in_order(P, dtype, d, shift):
+    """Lists longer than one look through them (512 entries), with repeats,
+    entries outside the sequence and rows outside every cluster, from rows on
+    any element boundary: exactly the fp32 sums in list order."""
+    torch = pytest.importorskip("torch")
+    batch, seq, K, k_max = 2, 900, 5, 1100
+    g = np.random.default_rng(d + shift)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def rows(seed):
+        flat = torch.from_numpy(np.random.default_rng(seed).standard_normal(batch * seq * d + shift).astype(np.float32))
+        return flat.to(td).cuda()[shift:].view(batch, seq, d)
+
+    hn, ho = rows(1), rows(2)
+    labels = g.integers(-1, K + 1, size=(batch, seq)).astype(np.int32)          # -1 and K: in no cluster
+    idx = g.integers(-2, seq + 2, size=(batch, k_max)).astype(np.int32)
+    cnt = np.array([k_max, 517], dtype=np.int32)
+    sums0 = g.standard_normal((batch, K, d)).astype(np.float32)
+    i32 = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    sums = torch.from_numpy(sums0.copy()).cuda()
+    P.cluster_update(hn, ho, i32(labels), i32(idx), i32(cnt), sums)
+    a, o = hn.float().cpu().numpy(), ho.float().cpu().numpy()
+    want = sums0.copy()
+    for b in range(batch):
+        acc = np.zeros((K, d), np.float32)
+        for p in idx[b, :cnt[b]]:
+            if 0 <= p < seq and 0 <= labels[b, p] < K:
+                acc[labels[b, p]] += a[b, p] - o[b, p]
+        want[b] += acc
+    assert np.array_equal(sums.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n_win,d", [(1, 4), (96, 260), (700, 256)])
+def test_cluster_means_in_window_order(P, n_win, d):
+    """Exactly the fp32 sums in window order times 1/count; an empty cluster
+    gives zeros."""
+    torch = pytest.importorskip("torch")
+    batch, seq, K = 2, 800, 7
+    g = np.random.default_rng(n_win)
+    x = g.standard_normal((batch, seq, d)).astype(np.float32)
+    win = np.stack([np.sort(g.permutation(seq)[:n_win]) for _ in range(batch)]).astype(np.int32)
+    labels = g.integers(0, K - 1, size=(batch, seq)).astype(np.int32)            # cluster K-1 empty
+    means = torch.full((batch, K, d), float("nan"), device="cuda")
+    P.cluster_means(torch.from_numpy(x).cuda(), torch.from_numpy(win).cuda(), torch.from_numpy(labels).cuda(), K, means)
+    want = np.zeros((batch, K, d), np.float32)
+    for b in range(batch):
+        cnt = np.zeros(K, np.int64)
+        for p in win[b]:
+            want[b, labels[b, p]] += x[b, p]
+            cnt[labels[b, p]] += 1
+        inv = np.where(cnt > 0, np.float32(1) / np.maximum(cnt, 1).astype(np.float32), np.float32(0))
+        want[b] *= inv[:, None].astype(np.float32)
+    np.testing.assert_allclose(means.cpu().numpy(), want, rtol=2.4e-7, atol=0)   # two fp32 steps: 1/n may round apart
