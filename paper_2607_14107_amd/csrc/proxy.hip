@@ -533,16 +533,23 @@ __global__ __launch_bounds__(kGramBlock) void kmeans_gram_kernel(const char* __r
         // assignment: cos(point i, centroid k) = sum_j C[k][j] G[i][j]
         gram_product(0);
         __syncthreads();
+        int moved = 0;
         for (int i = t; i < n; i += kGramBlock) {
             int best = 0;
             float bv = -INFINITY;
             for (int k = 0; k < K; ++k)
                 if (cosv[i][k] > bv) { bv = cosv[i][k]; best = k; }   // strict: lowest cluster on ties
+            moved |= it == 0 || lab[i] != best;
             lab[i] = best;
         }
         if (t < kMaxClusters) cnt_s[t] = 0;
-        __syncthreads();
-        if (it == iters) break;                          // the last round only assigns
+        moved = __syncthreads_or(moved);
+        // The last round only assigns.  So does one that moves no point: its
+        // labels are those the centroids were formed from, so forming them
+        // again gives the same bits and every later round the same labels
+        // (16 windows of 96 positions in 8 groups, 10 rounds: 56.6 us for all
+        // of them, 17.7 us for the ones that move a point).
+        if (it == iters || !moved) break;
         // update: |sum of the members' directions|^2 = sum over member pairs of
         // G; a cluster's wave also counts its members
         gram_product(1);
