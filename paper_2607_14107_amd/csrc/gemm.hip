@@ -59,6 +59,7 @@
 
 #include "gemm_dev.hpp"
 #include "host_common.hpp"
+#include "polestar_forward.h"
 
 namespace ps {
 namespace {
@@ -256,6 +257,11 @@ __global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) {
     tile_body<MI, NJ>(g, blockIdx.x);
 }
 
+template <int MI, int NJ>
+__global__ __launch_bounds__(kTileThreads) void gemm_swiglu_kernel(GemmArgs g) {
+    tile_body<MI, NJ, true>(g, blockIdx.x);
+}
+
 // Sum of the split-K partials, in split order (deterministic): thread ->
 // (column tile, row, 8 columns) so that consecutive threads read consecutive
 // 32-byte pieces of the contiguous partial tiles; the partial and row-map
@@ -422,14 +428,14 @@ static int quoted_split(bool bf16, long m_max, int N, int K) {
 // ks splits of `steps` K tiles: ceil(tiles * ks / 256) rounds of one workgroup
 // per CU, each a fixed cost (launch, row map, first DMA, stores) and its K
 // tiles at the shape's time, measured with every CU busy (12288 x 8192 x
-// 4096); a split run adds the reduction's launch and its fp32 partials
+// 4096; 256 x 192 tiles 512 x 24576 x 4096); a split run adds the reduction's launch and its fp32 partials
 // written and read back (512 x 4096 x 4096 in 2 and 4 splits, 512 x 4096 x
 // 12288 in 4 and 8).
 static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_max, int N) {
     double kt = 0.0;
     switch (10 * mi + nj) {
         case 84: kt = 1.52; break;
-        case 83: kt = 1.25; break;
+        case 83: kt = 1.40; break;
         case 64: kt = 1.27; break;
         case 82: kt = 0.87; break;
         case 44: kt = 0.89; break;
@@ -622,6 +628,48 @@ static bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream
     }
 }
 
+// Estimated time of a tile plan for m rows.
+static double plan_cost(const GemmPlan& p, long m, int N) {
+    const long tiles = static_cast<long>(ceil_div(m, 32 * p.tile_mi)) * ceil_div(N, 64 * p.tile_nj);
+    return tile_cost(p.tile_mi, p.tile_nj, tiles, p.ksplit, p.steps_per_split, m, N);
+}
+
+// The SwiGLU form runs where the plan is unsplit and its tile shape pairs
+// gate and up columns; 192-column plans take the cheapest shape that does, when
+// its estimate is no more above theirs than the separate pass would cost
+// (launch, and 6 bytes per feature at 5 TB/s: 512 rows of 12288 features 11.7
+// us) less the 1.5 us that the longer epilogue takes.
+bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream) {
+    if (!plan.tile || plan.ksplit > 1 || g.N % 32 != 0) return false;
+    GemmPlan p = plan;
+    const int nkt = g.K / 64;
+    double best = 1e30;
+#define PS_CASE(MI, NJ)                                                                                          \
+    {                                                                                                            \
+        const long tiles = static_cast<long>(ceil_div(g.m_max, 32 * MI)) * ceil_div(g.N, 64 * NJ);               \
+        const double cost = tile_cost(MI, NJ, tiles, 1, nkt, g.m_max, g.N);                                      \
+        if (cost < best) {                                                                                       \
+            best = cost;                                                                                         \
+            p.tile_mi = MI;                                                                                      \
+            p.tile_nj = NJ;                                                                                      \
+            p.row_tiles = ceil_div(g.m_max, 32 * MI);                                                            \
+            p.grid = static_cast<int>(tiles);                                                                    \
+        }                                                                                                        \
+    }
+    PS_SWIGLU_SHAPES(PS_CASE)
+#undef PS_CASE
+    if (best > plan_cost(plan, g.m_max, g.N) + 2.5 + 3.0 * g.m_max * g.N / 5e6) return false;
+    gemm_finalize_args(p, g);
+    const dim3 grid(p.grid), block(kTileThreads);
+    switch (10 * p.tile_mi + p.tile_nj) {
+#define PS_CASE(MI, NJ) \
+        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_swiglu_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
+        PS_SWIGLU_SHAPES(PS_CASE)
+#undef PS_CASE
+        default: return false;
+    }
+}
+
 polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t stream, GemmArgs* deferred) {
     gemm_finalize_args(p, g);
     bool ok;
@@ -643,12 +691,6 @@ polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t s
     else
         hipLaunchKernelGGL((gemm_reduce_kernel<false>), dim3(blocks), dim3(kGemmBlock), 0, stream, g);
     return launch_status();
-}
-
-// Estimated time of a tile plan for m rows.
-static double plan_cost(const GemmPlan& p, long m, int N) {
-    const long tiles = static_cast<long>(ceil_div(m, 32 * p.tile_mi)) * ceil_div(N, 64 * p.tile_nj);
-    return tile_cost(p.tile_mi, p.tile_nj, tiles, p.ksplit, p.steps_per_split, m, N);
 }
 
 // Half the capacity is the line because a packet holds the members of half the
@@ -715,6 +757,44 @@ extern "C" polestar_status polestar_refresh_kv(polestar_dtype dtype, int batch, 
     const GemmArgs g = refresh_gemm_args(batch, seq, d, kvd, h_cur, stale_idx, stale_count, k_max, block_start,
                                          block_len, w_k, w_v, k_cache, v_cache, workspace);
     return gemm_run_refresh(bf16, p, g, stream);
+}
+
+extern "C" size_t polestar_project_qkv_workspace_size(polestar_dtype dtype, int batch, int d, int n_heads,
+                                                      int n_kv_heads, int head_dim, int n_rows) {
+    using namespace ps;
+    if (!dtype_ok(dtype) || batch <= 0 || d <= 0 || n_heads <= 0 || n_kv_heads <= 0 || head_dim <= 0 || n_rows <= 0)
+        return 0;
+    return gemm_plan(dtype == POLESTAR_BF16, static_cast<long>(batch) * n_rows,
+                     (n_heads + 2 * n_kv_heads) * head_dim, d).ws_bytes;
+}
+
+extern "C" polestar_status polestar_project_qkv(polestar_dtype dtype, int batch, int seq, int d, int n_heads,
+                                                int n_kv_heads, int head_dim, const void* h_cur, int row_start,
+                                                int n_rows, const void* w_q, const void* w_k, const void* w_v,
+                                                void* q, void* k_cache, void* v_cache, void* workspace,
+                                                size_t workspace_bytes, hipStream_t stream) {
+    using namespace ps;
+    if (!dtype_ok(dtype) || batch <= 0 || seq <= 0 || d <= 0 || n_heads <= 0 || n_kv_heads <= 0 ||
+        head_dim <= 0 || n_rows <= 0 || row_start < 0 || row_start > seq - n_rows || !h_cur || !w_q || !w_k ||
+        !w_v || !q || !k_cache || !v_cache)
+        return POLESTAR_ERR_INVALID_ARGUMENT;
+    const bool bf16 = dtype == POLESTAR_BF16;
+    if ((head_dim != 64 && head_dim != 128) || !gemm_k_ok(bf16, d) || !aligned16(h_cur) || !aligned16(w_q) ||
+        !aligned16(w_k) || !aligned16(w_v) || !aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) ||
+        !aligned16(workspace) || batch > 65535)
+        return POLESTAR_ERR_UNSUPPORTED;
+    const long m_max = static_cast<long>(batch) * n_rows;
+    if (m_max > 0x7fffffffL / 4) return POLESTAR_ERR_UNSUPPORTED;
+    const int kvd = n_kv_heads * head_dim;
+    GemmArgs g = refresh_gemm_args(batch, seq, d, kvd, h_cur, nullptr, nullptr, 0, row_start, n_rows, w_k, w_v,
+                                   k_cache, v_cache, workspace);
+    g.w2 = static_cast<const char*>(w_q);
+    g.n1 = 2 * kvd;
+    g.out2 = static_cast<char*>(q);
+    g.N = 2 * kvd + n_heads * head_dim;
+    const GemmPlan p = gemm_plan(bf16, m_max, g.N, d);
+    if (workspace_bytes < p.ws_bytes || (p.ws_bytes > 0 && !workspace)) return POLESTAR_ERR_WORKSPACE;
+    return gemm_run(bf16, p, g, stream);
 }
 
 // ---------------------------------------------------------------------------

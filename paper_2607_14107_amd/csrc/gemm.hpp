@@ -13,7 +13,8 @@ namespace ps {
 
 enum GemmMode : int { kGemmRefresh = 0, kGemmBlockRows = 1 };
 
-// Y[m][n] = sum_k X[row(m)][k] * W[n][k], W = w0 for n < n0, else w1 (row n - n0).
+// Y[m][n] = sum_k X[row(m)][k] * W[n][k], W = w0 for n < n0, else w1 (row n - n0)
+// or, where there is a w2, w1 up to n1 and w2 (row n - n1) after it.
 struct GemmArgs {
     const char* x;        // [batch][seq][K] input rows
     const char* w0;
@@ -27,7 +28,10 @@ struct GemmArgs {
     int k_max;
     int block_start, block_len;
     char* out0;   // refresh: k_cache (row pitch n0); block rows: [rows][N]
-    char* out1;   // refresh: v_cache (row pitch N - n0)
+    char* out1;   // refresh: v_cache (row pitch N - n0, or n1 - n0)
+    const char* w2;     // third weight matrix (refresh mode without lists): its outputs are
+    int n1;             // dense rows out2[m][N - n1]
+    char* out2;
     float* ws;          // split-K partials [split][col_tile][m_max][128] fp32
     int* rowmap;        // split-K: [m_max][2] (sequence, position) of row m, -1: none
     int m_max;
@@ -69,6 +73,11 @@ inline bool gemm_k_ok(bool bf16, int K) { return K > 0 && K % (bf16 ? 128 : 64) 
 // POLESTAR_OK or a launch error.
 polestar_status gemm_run(bool bf16, const GemmPlan& plan, GemmArgs g, hipStream_t stream,
                          GemmArgs* deferred = nullptr);
+
+// silu(gate) * up of W = [gate; up] ([2 F][K], N = 2 F) for dense rows into
+// out0 [rows][F], in one launch; false (nothing enqueued) where the plan splits
+// K or its kernel has no such form.
+bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream);
 
 // gemm_run of a refresh (refresh_gemm_args).  Lists without a block are update
 // packets, sized for the whole window and usually about half full: their used

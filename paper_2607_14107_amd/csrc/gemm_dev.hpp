@@ -65,7 +65,9 @@ __device__ __forceinline__ char* out_ptr(const GemmArgs& g, int b, int pos, int 
         return g.out0 + (static_cast<size_t>(m) * g.N + n) * es;
     const size_t row = static_cast<size_t>(b) * g.seq + pos;
     if (n < g.n0) return g.out0 + (row * g.n0 + n) * es;
-    return g.out1 + (row * (g.N - g.n0) + (n - g.n0)) * es;
+    if (!g.w2) return g.out1 + (row * (g.N - g.n0) + (n - g.n0)) * es;
+    if (n < g.n1) return g.out1 + (row * (g.n1 - g.n0) + (n - g.n0)) * es;
+    return g.out2 + (static_cast<size_t>(m) * (g.N - g.n1) + (n - g.n1)) * es;
 }
 
 // 8 consecutive fp32 values -> destination (16-byte bf16 or 2x16-byte fp32 store).
@@ -85,8 +87,9 @@ __device__ __forceinline__ void store8(char* dst, const float* v) {
 // Weight row of output column n (nullptr past N).
 __device__ __forceinline__ const char* weight_row(const GemmArgs& g, int n, int es) {
     if (n >= g.N) return nullptr;
-    return n < g.n0 ? g.w0 + static_cast<size_t>(n) * g.K * es
-                    : g.w1 + static_cast<size_t>(n - g.n0) * g.K * es;
+    if (n < g.n0) return g.w0 + static_cast<size_t>(n) * g.K * es;
+    if (g.w2 && n >= g.n1) return g.w2 + static_cast<size_t>(n - g.n1) * g.K * es;
+    return g.w1 + static_cast<size_t>(n - g.n0) * g.K * es;
 }
 
 // ---------------------------------------------------------------------------
@@ -549,9 +552,19 @@ __device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, 
 #define PS_TILE_SHAPES(X) X(8, 4) X(8, 3) X(8, 2) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) \
     X(2, 4) X(2, 2)
 
+// The shapes of the SwiGLU form (an even number of column tiles per wave).
+#define PS_SWIGLU_SHAPES(X) X(8, 4) X(6, 4) X(4, 4) X(8, 2) X(6, 2) X(4, 2)
+
 // MI x NJ: 16 x 16 MFMA tiles per wave (BM = 32 MI rows, BN = 64 NJ columns
 // per workgroup).
-template <int MI, int NJ>
+//
+// SWI: W is [2 F][K], gate rows over up rows, and the output is
+// silu(gate) * up, [rows][F]: each wave's columns are NJ/2 tiles of gate
+// features and the same features' NJ/2 tiles of up, so a lane holds both of a
+// pair.  Unsplit, dense rows, F a multiple of 16.  gate and up are rounded to
+// bf16 first, as the separate product stores them; exp and the reciprocal are
+// the hardware's (1 ulp), under the bf16 rounding of the result.
+template <int MI, int NJ, bool SWI = false>
 __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
     static_assert(MI % 2 == 0 && MI >= 2 && MI <= 8 && NJ >= 2 && NJ <= 4, "64 to 256 rows, 128 to 256 columns");
     constexpr int ES = 2;                                // bf16 operands
@@ -622,7 +635,13 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
 #pragma unroll
     for (int i = 0; i < BI; ++i) {
         const int r = 8 * (w + 8 * i) + (lane >> 3);
-        const char* row = weight_row(g, n0 + r, ES);
+        int n = n0 + r;
+        if constexpr (SWI) {
+            const int F = g.N / 2, c = r % (16 * NJ);    // column c of its wave: gate, then up
+            const int f = (n0 + r - c) / 2 + c % (8 * NJ);
+            n = f < F ? f + (c < 8 * NJ ? 0 : F) : g.N;
+        }
+        const char* row = weight_row(g, n, ES);
         bsrc[i] = (row ? row : g.w0) + k0b + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
     // DMA instructions d0 .. d0+n-1 of K tile kt (past the split: its last tile again)
@@ -764,6 +783,46 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
     __builtin_amdgcn_s_waitcnt(0);                       // every DMA (the re-read tail too) has landed
     __syncthreads();                                     // and every wave is done with the slots
 
+    if constexpr (SWI) {
+        constexpr int NP = NJ / 2;                       // pairs of column tiles
+        constexpr int EP = 32 * NP + 16;                 // bytes of a staged row
+        constexpr int ER = 16 * HA;
+        constexpr int CPR = 2 * NP;                      // 16-byte chunks of a row
+        char* ep = (w < 2 ? sa0 : w < 4 ? sa1 : w < 6 ? sb0 : sb1) + (w & 1) * ER * EP;
+        const int F = g.N / 2, f0 = n0 / 2 + 16 * NP * wn;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+            for (int i = 0; i < HA; ++i)
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float gt = bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j][e], 0.f)));
+                        const float up =
+                            bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j + NP][e], 0.f)));
+                        v[e] = gt * __builtin_amdgcn_rcpf(1.f + fast_exp2(-kLog2e * gt)) * up;
+                    }
+                    *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
+                        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+                }
+            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < (ER * CPR + 63) / 64; ++q) {
+                const int idx = 64 * q + lane;
+                if (ER * CPR % 64 != 0 && idx >= ER * CPR) break;
+                const int r = idx / CPR, c = (idx % CPR) * 8;
+                const int lr = 16 * (MI * wm + HA * hh) + r;
+                if (rowb[lr] >= 0 && f0 + c < F)
+                    st16(g.out0 + (static_cast<size_t>(m0 + lr) * F + f0 + c) * 2, ld16(ep + r * EP + 2 * c));
+            }
+            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            __builtin_amdgcn_wave_barrier();
+        }
+        return;
+    }
     const int cbase = n0 + 16 * NJ * wn;
     if (g.ksplit > 1) {
         // fp32 partials straight from registers: 64 contiguous bytes of 16 rows per store

@@ -192,6 +192,7 @@ class Denoiser:
                       P.attention_drift_workspace_size(b, S, B, H)]
         for m in row_counts:
             sizes += [P.refresh_kv_workspace_size(c, b, d, H, hd, 0, m), P.project_q_workspace_size(c, b, d, H, hd, m),
+                      P.project_qkv_workspace_size(c, b, d, H, H, hd, m),
                       P.attend_workspace_size(c, b, S, d, H, H, hd, m),
                       P.linear_workspace_size(c, b, m, d, H * hd), P.linear_workspace_size(c, b, m, 2 * F, d),
                       P.linear_workspace_size(c, b, m, d, F)]
@@ -217,8 +218,11 @@ class Denoiser:
         P.embed(self.y, lo, m, w["tok_emb"], w["pos_emb"], x)
         if self.packet and mode == "all":
             self._rng_idx, self._rng_cnt = self._range(lo, m)
+        # without the packets' copies and a trace of every layer's state, a
+        # layer's last residual add leaves the next layer's normed rows too
+        chain = trace is None and not self.packet
         for li in range(sh.n_layers):
-            self._layer(li, x, lo, m, mode, block, k_top, trace, fwd)
+            self._layer(li, x, lo, m, mode, block, k_top, trace, fwd, chain and li > 0, chain and li + 1 < sh.n_layers)
 
     def _range(self, lo: int, m: int):
         """Positions [lo, lo + m) of every sequence as an index list."""
@@ -226,9 +230,10 @@ class Denoiser:
         return idx, torch.full((self.b,), m, dtype=torch.int32, device=self.dev)
 
     def _layer(self, li: int, x: torch.Tensor, lo: int, m: int, mode: str, block: tuple[int, int], k_top: int,
-               trace, fwd: int) -> None:
+               trace, fwd: int, normed: bool = False, norm_next: bool = False) -> None:
         """Layer li over the rows [lo, lo + m) whose inputs x [b][m][d] hold; x
-        receives the outputs."""
+        receives the outputs.  normed: h_cur holds the inputs' RMSNorm;
+        norm_next: leave the outputs' there."""
         sh, b, w = self.shape, self.b, self.w
         d, H, hd, F = sh.d, sh.n_heads, sh.head_dim, sh.ffn
         bs, bl = block
@@ -241,7 +246,8 @@ class Denoiser:
             before = dict(x=x.clone(), k=self.k[li].clone(), v=self.v[li].clone(), h=self.hc[li].clone())
         if self.packet and mode == "all":
             P.scatter_rows(x, self._rng_idx, self._rng_cnt, self.X[li])      # cache the layer inputs
-        P.rmsnorm(x, 0, m, self.h_cur, lo)
+        if not normed:
+            P.rmsnorm(x, 0, m, self.h_cur, lo)
         if mode == "refresh" or (li == sh.n_layers - 1 and not self.packet):
             P.drift(self.h_cur, self.hc[li], self.drift)
         if mode == "all":
@@ -254,18 +260,24 @@ class Denoiser:
         else:
             idx = cnt = None
             rb, rl = bs, bl
-        P.refresh_kv(self.h_cur, idx, cnt, rb, rl, lw["w_k"], lw["w_v"], self.k[li], self.v[li],
-                     workspace=self.ws)
-        P.copy_rows(self.h_cur, self.hc[li], idx, cnt, rb, rl)
-        P.project_q(self.h_cur, lw["w_q"], lo, m, H, out=q, workspace=self.ws)
+        if idx is None and (rb, rl) == (lo, m):          # every row rewritten: one product
+            P.project_qkv(self.h_cur, lo, m, lw["w_q"], lw["w_k"], lw["w_v"], q, self.k[li], self.v[li],
+                          workspace=self.ws)
+            P.copy_rows(self.h_cur, self.hc[li], idx, cnt, rb, rl)
+        else:
+            P.refresh_kv(self.h_cur, idx, cnt, rb, rl, lw["w_k"], lw["w_v"], self.k[li], self.v[li],
+                         workspace=self.ws)
+            P.copy_rows(self.h_cur, self.hc[li], idx, cnt, rb, rl)
+            P.project_q(self.h_cur, lw["w_q"], lo, m, H, out=q, workspace=self.ws)
         P.attend(None, None, self.k[li], self.v[li], lo, m, H, q_buf=q, out=o, workspace=self.ws)
         P.linear(o.view(b, m, H * hd), 0, m, lw["w_o"], t, workspace=self.ws)
-        P.residual_add(x, t)
-        P.rmsnorm(x, 0, m, g, 0)
-        P.linear(g, 0, m, lw["w_gu"], gu, workspace=self.ws)
-        P.swiglu(gu, a)
+        P.residual_rmsnorm(x, t, g, 0)
+        P.linear_swiglu(g, 0, m, lw["w_gu"], gu, a, workspace=self.ws)
         P.linear(a, 0, m, lw["w_down"], t, workspace=self.ws)
-        P.residual_add(x, t)
+        if norm_next:
+            P.residual_rmsnorm(x, t, self.h_cur, lo)
+        else:
+            P.residual_add(x, t)
         if trace is not None:
             trace(dict(event="layer", forward=fwd, layer=li, mode=mode, lo=lo, hi=lo + m, block=block,
                        k_top=k_top, before=before,
@@ -344,10 +356,8 @@ class Denoiser:
         P.project_q(hs, lw["w_q"], 0, k, H, out=q, workspace=self.ws)
         P.attend(None, None, self.k[li], self.v[li], 0, k, H, q_buf=q, out=o, workspace=self.ws)
         P.linear(o.view(b, k, H * hd), 0, k, lw["w_o"], t, workspace=self.ws)
-        P.residual_add(xs, t)
-        P.rmsnorm(xs, 0, k, g, 0)
-        P.linear(g, 0, k, lw["w_gu"], gu, workspace=self.ws)
-        P.swiglu(gu, a)
+        P.residual_rmsnorm(xs, t, g, 0)
+        P.linear_swiglu(g, 0, k, lw["w_gu"], gu, a, workspace=self.ws)
         P.linear(a, 0, k, lw["w_down"], t, workspace=self.ws)
         P.residual_add(xs, t)
 

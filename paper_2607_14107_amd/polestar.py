@@ -79,6 +79,10 @@ def lib() -> ctypes.CDLL:
     L.polestar_refresh_kv_noalloc_max_bytes.restype = Z
     L.polestar_refresh_kv_noalloc.argtypes = [I, I, I, I, I, I, P, P, P, I, I, I, P, P, P, P, P]
     L.polestar_refresh_kv_noalloc.restype = S
+    L.polestar_project_qkv_workspace_size.restype = Z
+    L.polestar_project_qkv_workspace_size.argtypes = [I, I, I, I, I, I, I]
+    L.polestar_project_qkv.restype = S
+    L.polestar_project_qkv.argtypes = [I, I, I, I, I, I, I, P, I, I, P, P, P, P, P, P, P, Z, P]
     L.polestar_project_q_workspace_size.restype = Z
     L.polestar_project_q_workspace_size.argtypes = [I, I, I, I, I, I]
     L.polestar_project_q.restype = S
@@ -134,6 +138,10 @@ def lib() -> ctypes.CDLL:
     L.polestar_linear.argtypes = [I, I, I, I, I, I, I, P, P, P, P, Z, P]
     L.polestar_swiglu.restype = S
     L.polestar_swiglu.argtypes = [I, Lg, I, P, P, P]
+    L.polestar_residual_rmsnorm.restype = S
+    L.polestar_residual_rmsnorm.argtypes = [I, I, I, I, P, P, F, P, I, I, P]
+    L.polestar_linear_swiglu.restype = S
+    L.polestar_linear_swiglu.argtypes = [I, I, I, I, I, I, I, P, P, P, P, P, Z, P]
     L.polestar_residual_add.restype = S
     L.polestar_residual_add.argtypes = [I, Lg, P, P, P]
     L.polestar_copy_rows.restype = S
@@ -257,6 +265,29 @@ def refresh_kv_noalloc(h_cur: torch.Tensor, stale_idx: torch.Tensor | None, stal
 
 def refresh_kv_noalloc_max_bytes() -> int:
     return lib().polestar_refresh_kv_noalloc_max_bytes()
+
+
+def project_qkv_workspace_size(dtype: int, batch: int, d: int, n_heads: int, n_kv_heads: int, head_dim: int,
+                               n_rows: int) -> int:
+    return lib().polestar_project_qkv_workspace_size(dtype, batch, d, n_heads, n_kv_heads, head_dim, n_rows)
+
+
+def project_qkv(h_cur: torch.Tensor, row_start: int, n_rows: int, w_q: torch.Tensor, w_k: torch.Tensor,
+                w_v: torch.Tensor, q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor,
+                workspace: torch.Tensor | None = None, stream=None) -> None:
+    """refresh_kv and project_q of the rows [row_start, row_start + n_rows) as one product."""
+    b, s, d = h_cur.shape
+    _, _, kvh, hd = k_cache.shape
+    heads = q.shape[2]
+    if tuple(q.shape) != (b, n_rows, heads, hd) or tuple(w_q.shape) != (heads * hd, d):
+        raise ValueError("project_qkv: shapes do not match")
+    dt = _dtype_code(h_cur)
+    ws = _workspace(project_qkv_workspace_size(dt, b, d, heads, kvh, hd, n_rows), h_cur.device, workspace)
+    nbytes = 0 if ws is None else ws.numel() * ws.element_size()
+    _check("polestar_project_qkv", lib().polestar_project_qkv(
+        dt, b, s, d, heads, kvh, hd, _ptr(h_cur), row_start, n_rows, _ptr(w_q, h_cur.dtype), _ptr(w_k, h_cur.dtype),
+        _ptr(w_v, h_cur.dtype), _ptr(q, h_cur.dtype), _ptr(k_cache, h_cur.dtype), _ptr(v_cache, h_cur.dtype),
+        _ptr(ws), nbytes, _stream(stream)))
 
 
 def project_q_workspace_size(dtype: int, batch: int, d: int, n_heads: int, head_dim: int,
@@ -435,6 +466,35 @@ def residual_add(x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.Tensor:
     _check("polestar_residual_add", lib().polestar_residual_add(
         _dtype_code(y), x.numel(), _ptr(x, torch.float32), _ptr(y), _stream(stream)))
     return x
+
+
+def residual_rmsnorm(x: torch.Tensor, y: torch.Tensor, out: torch.Tensor, out_start: int, eps: float = 1e-5,
+                     stream=None) -> torch.Tensor:
+    """x += y, then out[b][out_start + r] = RMSNorm(x[b][r]); x, y [batch][n_rows][d], out [batch][seq][d]."""
+    b, n, d = x.shape
+    if tuple(y.shape) != (b, n, d) or out.shape[0] != b or out.shape[2] != d:
+        raise ValueError("residual_rmsnorm: shapes do not match")
+    _check("polestar_residual_rmsnorm", lib().polestar_residual_rmsnorm(
+        _dtype_code(out), b, n, d, _ptr(x, torch.float32), _ptr(y, out.dtype), eps, _ptr(out), out.shape[1], out_start,
+        _stream(stream)))
+    return out
+
+
+def linear_swiglu(x: torch.Tensor, row_start: int, n_rows: int, w_gate_up: torch.Tensor, gate_up: torch.Tensor,
+                  out: torch.Tensor, workspace: torch.Tensor | None = None, stream=None) -> torch.Tensor:
+    """out[b][r] = silu(gate) * up of W_gate_up x[b][row_start + r]; gate_up [batch][n_rows][2F] is scratch."""
+    b, seq, n_in = x.shape
+    f = out.shape[-1]
+    if (tuple(out.shape) != (b, n_rows, f) or gate_up.numel() != 2 * out.numel()
+            or tuple(w_gate_up.shape) != (2 * f, n_in)):
+        raise ValueError("linear_swiglu: shapes do not match")
+    dt = _dtype_code(x)
+    ws = _workspace(linear_workspace_size(dt, b, n_rows, 2 * f, n_in), x.device, workspace)
+    nbytes = 0 if ws is None else ws.numel() * ws.element_size()
+    _check("polestar_linear_swiglu", lib().polestar_linear_swiglu(
+        dt, b, seq, n_in, f, row_start, n_rows, _ptr(x), _ptr(w_gate_up, x.dtype), _ptr(gate_up, x.dtype),
+        _ptr(out, x.dtype), _ptr(ws), nbytes, _stream(stream)))
+    return out
 
 
 def copy_rows(src: torch.Tensor, dst: torch.Tensor, stale_idx: torch.Tensor | None,

@@ -287,3 +287,64 @@ def test_refresh_packed_lists(P, batch, k_max, counts):
                 want = h[b, rows].float() @ w.float().t()
                 err = (got[b, rows].reshape(len(rows), -1).float() - want).abs().amax(1) / want.abs().amax(1)
                 assert float(err.max()) <= 5e-3, (b, counts, float(err.max()))
+
+
+@pytest.mark.parametrize("batch,n,d,ffn", [
+    (16, 32, 1024, 3072), (1, 300, 512, 1040), (3, 111, 3584, 4736), (2, 700, 384, 2064), (1, 1500, 256, 4096),
+    (4, 8, 512, 768), (1, 2400, 512, 3088),
+])
+def test_linear_swiglu_against_its_calls(P, batch, n, d, ffn):
+    """One launch (unsplit plans of the tile kernel) or the two calls: either
+    way within a bf16 step (2^-8, and one for the gate's and up's own rounding
+    landing apart) of silu(gate) * up on the rounded fp32 products."""
+    torch = pytest.importorskip("torch")
+    gen = torch.Generator(device="cuda").manual_seed(n + ffn)
+    x = torch.randn((batch, n + 5, d), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * ffn, d), generator=gen, device="cuda") * 2 / d ** 0.5).to(torch.bfloat16)
+    gu = torch.empty((batch, n, 2 * ffn), dtype=torch.bfloat16, device="cuda")
+    a = torch.full((batch, n, ffn), float("nan"), dtype=torch.bfloat16, device="cuda")
+    P.linear_swiglu(x, 3, n, w, gu, a)
+    p = (x[:, 3:3 + n].reshape(-1, d).float() @ w.float().t()).to(torch.bfloat16).float()
+    want = (p[:, :ffn] * torch.sigmoid(p[:, :ffn]) * p[:, ffn:]).view(batch, n, ffn)
+    err = (a.float() - want).abs().amax(2) / want.abs().amax(2)
+    assert float(err.max()) <= 2 * 2 ** -8, (batch, n, d, ffn, float(err.max()))
+
+
+@pytest.mark.parametrize("dtype,batch,n,d,H,kv,hd", [
+    ("bf16", 16, 32, 512, 8, 8, 64), ("bf16", 1, 32, 1024, 8, 2, 128), ("bf16", 3, 50, 512, 4, 4, 128),
+    ("bf16", 2, 400, 256, 16, 4, 64), ("bf16", 1, 9, 256, 4, 1, 64), ("fp32", 2, 60, 128, 4, 2, 64),
+])
+def test_project_qkv_against_its_calls(P, dtype, batch, n, d, H, kv, hd):
+    torch = pytest.importorskip("torch")
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    rnd = lambda *sh: torch.randn(sh, generator=gen, device="cuda").to(td)  # noqa: E731
+    seq, lo = n + 20, 7
+    h = rnd(batch, seq, d)
+    wq, wk, wv = rnd(H * hd, d) * 0.05, rnd(kv * hd, d) * 0.05, rnd(kv * hd, d) * 0.05
+    k0, v0 = rnd(batch, seq, kv, hd), rnd(batch, seq, kv, hd)
+    k, v, q = k0.clone(), v0.clone(), torch.full((batch, n, H, hd), float("nan"), dtype=td, device="cuda")
+    P.project_qkv(h, lo, n, wq, wk, wv, q, k, v)
+    rows = h[:, lo:lo + n].double()
+    tol = 5e-3 if dtype == "bf16" else 1e-5            # one rounding to bf16 / fp32 sums
+    for got, w in ((q, wq), (k[:, lo:lo + n], wk), (v[:, lo:lo + n], wv)):
+        want = rows @ w.double().t()
+        err = (got.reshape(batch, n, -1).double() - want).abs().amax(2) / want.abs().amax(2)
+        assert float(err.max()) <= tol, (dtype, n, float(err.max()))
+    for got, was in ((k, k0), (v, v0)):
+        assert torch.equal(got[:, :lo], was[:, :lo]) and torch.equal(got[:, lo + n:], was[:, lo + n:])
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 4096), ("bf16", 260), ("fp32", 1028), ("fp32", 9000)])
+def test_residual_rmsnorm_is_its_two_calls(P, dtype, d):
+    torch = pytest.importorskip("torch")
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((3, 37, d), generator=gen, device="cuda")
+    t = torch.randn((3, 37, d), generator=gen, device="cuda").to(td)
+    x2, out = x.clone(), torch.zeros((3, 50, d), dtype=td, device="cuda")
+    out2 = out.clone()
+    P.residual_add(x, t)
+    P.rmsnorm(x, 0, 37, out, 11)
+    P.residual_rmsnorm(x2, t, out2, 11)
+    assert torch.equal(x, x2) and torch.equal(out, out2)
