@@ -252,16 +252,6 @@ __global__ __launch_bounds__(kGemmBlock) void gemm_dma_kernel(GemmArgs g) {
     dma_body<true, MT, NST, 4, NTW>(g, blockIdx.x);
 }
 
-template <int MI, int NJ>
-__global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) {
-    tile_body<MI, NJ>(g, blockIdx.x);
-}
-
-template <int MI, int NJ>
-__global__ __launch_bounds__(kTileThreads) void gemm_swiglu_kernel(GemmArgs g) {
-    tile_body<MI, NJ, true>(g, blockIdx.x);
-}
-
 // Sum of the split-K partials, in split order (deterministic): thread ->
 // (column tile, row, 8 columns) so that consecutive threads read consecutive
 // 32-byte pieces of the contiguous partial tiles; the partial and row-map
@@ -616,18 +606,6 @@ int gemm_reduce_blocks(const GemmPlan& p, const GemmArgs& g) {
     return ceil_div(static_cast<long>(p.col_tiles) * g.m_max * 16, kGemmBlock);
 }
 
-// The tile kernel of the plan's tile shape (false for a shape not instantiated).
-static bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream) {
-    const dim3 grid(p.grid), block(kTileThreads);
-    switch (10 * p.tile_mi + p.tile_nj) {
-#define PS_CASE(MI, NJ) \
-        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_tile_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
-        PS_TILE_SHAPES(PS_CASE)
-#undef PS_CASE
-        default: return false;
-    }
-}
-
 // Estimated time of a tile plan for m rows.
 static double plan_cost(const GemmPlan& p, long m, int N) {
     const long tiles = static_cast<long>(ceil_div(m, 32 * p.tile_mi)) * ceil_div(N, 64 * p.tile_nj);
@@ -660,14 +638,7 @@ bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream) {
 #undef PS_CASE
     if (best > plan_cost(plan, g.m_max, g.N) + 2.5 + 3.0 * g.m_max * g.N / 5e6) return false;
     gemm_finalize_args(p, g);
-    const dim3 grid(p.grid), block(kTileThreads);
-    switch (10 * p.tile_mi + p.tile_nj) {
-#define PS_CASE(MI, NJ) \
-        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_swiglu_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
-        PS_SWIGLU_SHAPES(PS_CASE)
-#undef PS_CASE
-        default: return false;
-    }
+    return launch_tile_swiglu(p, g, stream);
 }
 
 polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t stream, GemmArgs* deferred) {

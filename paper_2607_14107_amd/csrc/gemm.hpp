@@ -79,6 +79,14 @@ polestar_status gemm_run(bool bf16, const GemmPlan& plan, GemmArgs g, hipStream_
 // K or its kernel has no such form.
 bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream);
 
+// The tile kernel's launches (gemm_tile.hip) for a plan's tile shape: the
+// product, its SwiGLU form, and the product with a split-K reduction of
+// another (n_qred gemm_reduce_blocks) behind it in the same launch.  False for
+// a shape that is not instantiated.
+bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream);
+bool launch_tile_swiglu(const GemmPlan& p, const GemmArgs& g, hipStream_t stream);
+bool launch_tile_qred(const GemmPlan& p, const GemmArgs& g, const GemmArgs& q, int n_qred, hipStream_t stream);
+
 // gemm_run of a refresh (refresh_gemm_args).  Lists without a block are update
 // packets, sized for the whole window and usually about half full: their used
 // rows are packed, and the plan for half the capacity runs where they fit it.

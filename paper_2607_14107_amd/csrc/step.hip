@@ -114,28 +114,6 @@ struct ReduceArgs {
     int n_r;
 };
 
-// refresh on the tile kernel, unsplit | Q split-K reduce: the tile
-// workgroups come first (tile_body's XCD-aware order counts from id 0), the
-// reduction's after them, on compute units the tiles leave free or as a short
-// tail, so the Q reduce needs no launch of its own (bf16 only, as the tile
-// kernel).
-struct TileQArgs {
-    GemmArgs r;    // refresh (n_tile workgroups, first)
-    GemmArgs q;    // Q projection
-    int n_tile;
-};
-
-static_assert(kTileThreads % kGemmBlock == 0, "a workgroup of the reduce role takes whole reduce blocks");
-
-template <int MI, int NJ>
-__global__ __launch_bounds__(kTileThreads) void tile_qred_kernel(TileQArgs k) {
-    if (static_cast<int>(blockIdx.x) < k.n_tile) {
-        tile_body<MI, NJ>(k.r, blockIdx.x);
-        return;
-    }
-    reduce_body<true>(k.q, static_cast<long>(blockIdx.x - k.n_tile) * kTileThreads + threadIdx.x);
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(kStepBlock) void reduce2_kernel(ReduceArgs k) {
     if (static_cast<int>(blockIdx.x) < k.n_r) {
@@ -454,19 +432,8 @@ extern "C" polestar_status polestar_step(const polestar_step_args* a, void* work
                                     a->k_cache, a->v_cache, ws);
     const int n_qred = gemm_reduce_blocks(L.qp, f.q);
     if (bf16 && L.rp.tile && L.rp.ksplit == 1 && n_qred > 0) {
-        TileQArgs tq{};
         gemm_finalize_args(L.rp, rg);
-        tq.r = rg;
-        tq.q = f.q;
-        tq.n_tile = L.rp.grid;
-        const dim3 grid(L.rp.grid + ceil_div(n_qred, kTileThreads / kGemmBlock)), block(kTileThreads);
-        switch (10 * L.rp.tile_mi + L.rp.tile_nj) {
-#define PS_CASE(MI, NJ) \
-            case 10 * MI + NJ: hipLaunchKernelGGL((tile_qred_kernel<MI, NJ>), grid, block, 0, stream, tq); break;
-            PS_TILE_SHAPES(PS_CASE)
-#undef PS_CASE
-            default: return POLESTAR_ERR_UNSUPPORTED;
-        }
+        if (!launch_tile_qred(L.rp, rg, f.q, n_qred, stream)) return POLESTAR_ERR_UNSUPPORTED;
         st = launch_status();
         if (st != POLESTAR_OK) return st;
     } else {
