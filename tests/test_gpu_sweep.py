@@ -4,10 +4,9 @@ and K/V-refresh entry points, each checked against the CPU oracle.
 The shapes are drawn so that every launch plan gets exercised: per-head and
 grouped-head attention (4 or 8 waves, idle waves, one or many key splits,
 ragged key tiles and query groups; the ring kernel for long key ranges), and
-the GEMM plans (small-M kernel, DMA kernel with up to eight row tiles and 8
-to 16 stages per split, row kernel, and through polestar_linear the tile
-kernel's 256- or 192-row by 256- or 192-column tiles) with ragged row tiles
-and refresh row counts.  Tolerances as in
+the GEMM plans (small-M kernel, DMA kernel, row kernel, and the tile kernel's
+64- to 256-row by 128- to 256-column tiles) with ragged row tiles and refresh
+row counts.  Tolerances as in
 test_gpu_parity: fp32 1e-4, bf16 2e-2 relative per (row, head); rows the
 refresh does not touch byte-identical.
 """
