@@ -437,7 +437,7 @@ static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_ma
         default: kt = 0.42; break;
     }
     const double rounds = static_cast<double>((tiles * ks + kTargetWgs - 1) / kTargetWgs);
-    return rounds * (steps * kt + 4.0) + (ks > 1 ? 5.0 + 4.0 * ks * m_max * N * 0.28e-6 : 0.0);
+    return rounds * (steps * kt + 4.0) + (ks > 1 ? 5.0 + 4.0 * ks * m_max * N * 0.32e-6 : 0.0);
 }
 
 // The tile kernel's plan: the tile shape and split with the least estimated
