@@ -612,31 +612,43 @@ static double plan_cost(const GemmPlan& p, long m, int N) {
     return tile_cost(p.tile_mi, p.tile_nj, tiles, p.ksplit, p.steps_per_split, m, N);
 }
 
-// The SwiGLU form runs where the plan is unsplit and its tile shape pairs
-// gate and up columns; 192-column plans take the cheapest shape that does, when
-// its estimate is no more above theirs than the separate pass would cost
-// (launch, and 6 bytes per feature at 5 TB/s: 512 rows of 12288 features 11.7
-// us) less the 1.5 us that the longer epilogue takes.
-bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream) {
-    if (!plan.tile || plan.ksplit > 1 || g.N % 32 != 0) return false;
-    GemmPlan p = plan;
-    const int nkt = g.K / 64;
+// The SwiGLU form's plan, false where two calls are faster (or the only way).
+// It runs where the product's plan is unsplit, in the cheapest tile shape that
+// pairs gate and up columns, when its estimate and its longer epilogue (expf
+// and a division per pair: 5.5 us for a round of 256 x 256 tiles, by the pairs
+// of a lane for smaller ones) are no more above the product's own plan than the
+// separate pass costs (6.5 us for its launch and the wait behind the product,
+// and 6 bytes per feature at 5 TB/s).  4096 channels to 2 x 12288, 1024 rows:
+// 171.8 us in one launch against 192.6 in two.  The line lies near 512 rows,
+// where one launch takes 192 tiles of 256 x 256 and two take 256 of 256 x 192
+// and the pass: 94.2 against 90.5 us repeated alone, but two layers and the head
+// of a forward 1106.6 against 1109.3 us.
+static bool swiglu_plan(const GemmPlan& plan, long m_max, int N, int K, GemmPlan& p) {
+    if (!plan.tile || plan.ksplit > 1 || N % 32 != 0) return false;
+    p = plan;
+    const int nkt = K / 64;
     double best = 1e30;
 #define PS_CASE(MI, NJ)                                                                                          \
     {                                                                                                            \
-        const long tiles = static_cast<long>(ceil_div(g.m_max, 32 * MI)) * ceil_div(g.N, 64 * NJ);               \
-        const double cost = tile_cost(MI, NJ, tiles, 1, nkt, g.m_max, g.N);                                      \
+        const long tiles = static_cast<long>(ceil_div(m_max, 32 * MI)) * ceil_div(N, 64 * NJ);                   \
+        const double rounds = static_cast<double>((tiles + kTargetWgs - 1) / kTargetWgs);                        \
+        const double cost = tile_cost(MI, NJ, tiles, 1, nkt, m_max, N) + rounds * (5.5 / 32) * (MI * NJ);        \
         if (cost < best) {                                                                                       \
             best = cost;                                                                                         \
             p.tile_mi = MI;                                                                                      \
             p.tile_nj = NJ;                                                                                      \
-            p.row_tiles = ceil_div(g.m_max, 32 * MI);                                                            \
+            p.row_tiles = ceil_div(m_max, 32 * MI);                                                              \
             p.grid = static_cast<int>(tiles);                                                                    \
         }                                                                                                        \
     }
     PS_SWIGLU_SHAPES(PS_CASE)
 #undef PS_CASE
-    if (best > plan_cost(plan, g.m_max, g.N) + 2.5 + 3.0 * g.m_max * g.N / 5e6) return false;
+    return best <= plan_cost(plan, m_max, N) + 6.5 + 3.0 * m_max * N / 5e6;
+}
+
+bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream) {
+    GemmPlan p;
+    if (!swiglu_plan(plan, g.m_max, g.N, g.K, p)) return false;
     gemm_finalize_args(p, g);
     return launch_tile_swiglu(p, g, stream);
 }
@@ -686,6 +698,29 @@ polestar_status gemm_run_refresh(bool bf16, const GemmPlan& p, GemmArgs g, hipSt
 }
 
 }  // namespace ps
+
+// What a product of m rows runs as, for tests that name the kernels they are
+// about (host only, not in the public headers).  out: kernel (0 small, 1 DMA, 2
+// tile, 3 rows), the tile kernel's rows and columns of a workgroup, splits of K.
+static void plan_info(const ps::GemmPlan& p, int* out) {
+    out[0] = p.small ? 0 : p.dma ? 1 : p.tile ? 2 : 3;
+    out[1] = p.tile ? 32 * p.tile_mi : 0;
+    out[2] = p.tile ? 64 * p.tile_nj : 0;
+    out[3] = p.ksplit;
+}
+
+extern "C" void ps_gemm_plan_info(int bf16, long m, int N, int K, int* out) {
+    plan_info(ps::gemm_plan(bf16 != 0, m, N, K), out);
+}
+
+// The same for the one-launch SwiGLU product of N = 2 ffn columns; 0 where
+// polestar_linear_swiglu makes two calls.
+extern "C" int ps_swiglu_plan_info(long m, int N, int K, int* out) {
+    ps::GemmPlan p;
+    if (!ps::swiglu_plan(ps::gemm_plan(true, m, N, K), m, N, K, p)) return 0;
+    plan_info(p, out);
+    return 1;
+}
 
 extern "C" size_t polestar_refresh_kv_workspace_size(polestar_dtype dtype, int batch, int d,
                                                      int n_kv_heads, int head_dim, int k_max,

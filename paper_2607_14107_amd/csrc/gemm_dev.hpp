@@ -562,8 +562,8 @@ __device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, 
 // silu(gate) * up, [rows][F]: each wave's columns are NJ/2 tiles of gate
 // features and the same features' NJ/2 tiles of up, so a lane holds both of a
 // pair.  Unsplit, dense rows, F a multiple of 16.  gate and up are rounded to
-// bf16 first, as the separate product stores them; exp and the reciprocal are
-// the hardware's (1 ulp), under the bf16 rounding of the result.
+// bf16 first, as the separate product stores them, and silu_mul is the separate
+// pass's: the same bits as that product and that pass.
 template <int MI, int NJ, bool SWI = false>
 __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
     static_assert(MI % 2 == 0 && MI >= 2 && MI <= 8 && NJ >= 2 && NJ <= 4, "64 to 256 rows, 128 to 256 columns");
@@ -802,7 +802,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
                         const float gt = bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j][e], 0.f)));
                         const float up =
                             bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j + NP][e], 0.f)));
-                        v[e] = gt * __builtin_amdgcn_rcpf(1.f + fast_exp2(-kLog2e * gt)) * up;
+                        v[e] = silu_mul(gt, up);
                     }
                     *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
                         make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));

@@ -159,9 +159,8 @@ __global__ __launch_bounds__(kRowBlock) void swiglu_kernel(const char* __restric
         const long c = 4 * (i - r * (F / 4));
         const char* row = gu + r * 2 * F * ES;
         const float4 g = ld4<BF16>(row, c), u = ld4<BF16>(row, F + c);
-        const float4 o = make_float4(g.x / (1.f + expf(-g.x)) * u.x, g.y / (1.f + expf(-g.y)) * u.y,
-                                     g.z / (1.f + expf(-g.z)) * u.z, g.w / (1.f + expf(-g.w)) * u.w);
-        st4<BF16>(out + r * F * ES, c, o);
+        st4<BF16>(out + r * F * ES, c,
+                  make_float4(silu_mul(g.x, u.x), silu_mul(g.y, u.y), silu_mul(g.z, u.z), silu_mul(g.w, u.w)));
     }
 }
 

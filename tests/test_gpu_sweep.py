@@ -11,6 +11,8 @@ test_gpu_parity: fp32 1e-4, bf16 2e-2 relative per (row, head); rows the
 refresh does not touch byte-identical.
 """
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -307,6 +309,44 @@ def test_linear_swiglu_against_its_calls(P, batch, n, d, ffn):
     want = (p[:, :ffn] * torch.sigmoid(p[:, :ffn]) * p[:, ffn:]).view(batch, n, ffn)
     err = (a.float() - want).abs().amax(2) / want.abs().amax(2)
     assert float(err.max()) <= 2 * 2 ** -8, (batch, n, d, ffn, float(err.max()))
+
+
+@pytest.mark.parametrize("n,d,ffn,tile", [
+    (65, 128, 144, (128, 128)), (529, 128, 3280, (192, 128)), (771, 128, 3280, (256, 128)),
+    (1044, 128, 3280, (128, 256)), (1041, 128, 3600, (192, 256)), (1546, 128, 3616, (256, 256)),
+    (529, 128, 3288, None),    # 2 ffn no multiple of 32: two calls
+    (200, 1536, 384, None),    # no tile kernel: two calls
+])
+def test_linear_swiglu_has_its_calls_values(P, n, d, ffn, tile):
+    """Every tile shape of the one-launch form (and the calls that take two)
+    has the values of polestar_linear and polestar_swiglu, bit for bit, over
+    gates that a shorter formula would treat differently: to +-120 in steps of a
+    quarter (the quotient's denominator passes 2^126 at -87.4 and overflows at
+    -88.7), zero, the largest finite values, and rows whose products are
+    infinite or NaN."""
+    info = (ctypes.c_int * 4)()
+    one_launch = P.lib().ps_swiglu_plan_info(ctypes.c_long(n), 2 * ffn, d, info)
+    assert (tuple(info)[1:3] if one_launch else None) == tile
+    torch = pytest.importorskip("torch")
+    x = torch.zeros((1, n, d), device="cuda")
+    x[0, :, 0] = torch.tensor([1.0, -1.0, 0.5, 4.0, 0.0, float("inf"), float("nan")], device="cuda")[
+        torch.arange(n, device="cuda") % 7]
+    w = torch.zeros((2 * ffn, d), device="cuda")
+    f = torch.arange(ffn, device="cuda")
+    w[:ffn, 0] = (f % 960 - 480) / 4.0
+    w[:ffn:97, 0], w[5:ffn:97, 0] = 3e38, -3e38
+    w[ffn:, 0] = torch.where(f % 2 == 0, 1.0, -3.0) * 2.0 ** (f % 5)
+    x, w = x.to(torch.bfloat16), w.to(torch.bfloat16)
+    gu = torch.empty((1, n, 2 * ffn), dtype=torch.bfloat16, device="cuda")
+    one, two = torch.empty((1, n, ffn), dtype=torch.bfloat16, device="cuda"), torch.empty(
+        (1, n, ffn), dtype=torch.bfloat16, device="cuda")
+    P.linear_swiglu(x, 0, n, w, gu, one)
+    P.linear(x, 0, n, w, gu)
+    P.swiglu(gu, two)
+    nan = torch.isnan(two)
+    assert bool(nan.any()) and torch.equal(torch.isnan(one), nan)
+    a, b = (t.view(torch.int16)[~nan] for t in (one, two))
+    assert torch.equal(a, b), (n, d, ffn, int((a != b).sum()))
 
 
 @pytest.mark.parametrize("dtype,batch,n,d,H,kv,hd", [
