@@ -42,6 +42,18 @@ typedef float float2_hw __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2_hw){lo, hi}, bf16x2_hw));
 }
+// Four floats to packed bf16 with pack_bf16x2's bits, NaN too: two compares in
+// the usual case, the selects only where a lane of the wave holds a NaN.
+__device__ __forceinline__ uint2 cvt4_bf16(float a, float b, float c, float d) {
+    if (__builtin_amdgcn_ballot_w64(__builtin_isunordered(a, b) || __builtin_isunordered(c, d))) {
+        const float nan = __uint_as_float(0x7fc00000u);
+        a = a == a ? a : nan;
+        b = b == b ? b : nan;
+        c = c == c ? c : nan;
+        d = d == d ? d : nan;
+    }
+    return make_uint2(cvt_pk_bf16(a, b), cvt_pk_bf16(c, d));
+}
 
 // Storage traits: E = element count of one 16-byte chunk.
 template <bool BF16> struct Elem;

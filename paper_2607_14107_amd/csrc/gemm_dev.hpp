@@ -805,7 +805,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
                         v[e] = silu_mul(gt, up);
                     }
                     *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
-                        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+                        cvt4_bf16(v[0], v[1], v[2], v[3]);
                 }
             __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
             __builtin_amdgcn_wave_barrier();
@@ -856,7 +856,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
             for (int j = 0; j < NJ; ++j) {
                 const floatx4 v = acc[HA * hh + i][j];
                 *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
-                    make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+                    cvt4_bf16(v[0], v[1], v[2], v[3]);
             }
         __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
         __builtin_amdgcn_wave_barrier();

@@ -343,10 +343,31 @@ def test_linear_swiglu_has_its_calls_values(P, n, d, ffn, tile):
     P.linear_swiglu(x, 0, n, w, gu, one)
     P.linear(x, 0, n, w, gu)
     P.swiglu(gu, two)
-    nan = torch.isnan(two)
-    assert bool(nan.any()) and torch.equal(torch.isnan(one), nan)
-    a, b = (t.view(torch.int16)[~nan] for t in (one, two))
+    a, b = one.view(torch.int16), two.view(torch.int16)
     assert torch.equal(a, b), (n, d, ffn, int((a != b).sum()))
+
+
+@pytest.mark.parametrize("m,N,K,kernel", [
+    (9, 256, 256, (0, 0, 0, 1)), (40, 4096, 4096, (1, 0, 0, 8)),
+    (529, 6560, 128, (2, 192, 128, 1)), (1546, 7232, 128, (2, 256, 256, 1)), (68, 4288, 2048, (2, 128, 128, 4)),
+])
+def test_linear_nan_bits(P, m, N, K, kernel):
+    """A NaN output is the quiet NaN 0x7fc0 from every kernel, whatever the
+    sign and payload of the operands', and reaches its own row only."""
+    torch = pytest.importorskip("torch")
+    info = (ctypes.c_int * 4)()
+    P.lib().ps_gemm_plan_info(1, ctypes.c_long(m), N, K, info)
+    assert tuple(info) == kernel
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    x = torch.randn((1, m, K), generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16)
+    clean = P.linear(x, 0, m, w, torch.empty((1, m, N), dtype=torch.bfloat16, device="cuda"))
+    rows = list(range(3, m, 5))
+    x.view(torch.int16)[0, rows, K // 3] = -63          # 0xffc1
+    y = P.linear(x, 0, m, w, torch.empty((1, m, N), dtype=torch.bfloat16, device="cuda"))
+    want = clean.view(torch.int16).clone()
+    want[0, rows] = 0x7fc0
+    assert torch.equal(y.view(torch.int16), want)
 
 
 @pytest.mark.parametrize("dtype,batch,n,d,H,kv,hd", [
