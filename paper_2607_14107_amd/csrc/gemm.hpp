@@ -13,8 +13,7 @@ namespace ps {
 
 enum GemmMode : int { kGemmRefresh = 0, kGemmBlockRows = 1 };
 
-// Y[m][n] = sum_k X[row(m)][k] * W[n][k], W = w0 for n < n0, else w1 (row n - n0)
-// or, where there is a w2, w1 up to n1 and w2 (row n - n1) after it.
+// Y[m][n] = sum_k X[row(m)][k] * W[n][k], W = w0 for n < n0, else w1 (row n - n0).
 struct GemmArgs {
     const char* x;        // [batch][seq][K] input rows
     const char* w0;
@@ -28,10 +27,7 @@ struct GemmArgs {
     int k_max;
     int block_start, block_len;
     char* out0;   // refresh: k_cache (row pitch n0); block rows: [rows][N]
-    char* out1;   // refresh: v_cache (row pitch N - n0, or n1 - n0)
-    const char* w2;     // third weight matrix (refresh mode without lists): its outputs are
-    int n1;             // dense rows out2[m][N - n1]
-    char* out2;
+    char* out1;   // refresh: v_cache (row pitch N - n0)
     float* ws;          // split-K partials [split][col_tile][m_max][128] fp32
     int* rowmap;        // split-K: [m_max][2] (sequence, position) of row m, -1: none
     int m_max;
@@ -42,6 +38,16 @@ struct GemmArgs {
     // kernel, unsplit): the lists' used entries alone, one sequence after the
     // other, and the launch returns unless rows_lo < their number <= rows_hi.
     int packed, rows_lo, rows_hi;
+};
+
+// Three weight matrices (refresh mode without lists): w1 up to column n1 (v_cache
+// has row pitch n1 - n0), then w2, whose outputs are dense rows out2[m][N - n1].
+// A type of its own, so that the kernels of two matrices do not test for a
+// third on every weight and output row.
+struct QkvGemmArgs : GemmArgs {
+    const char* w2;
+    int n1;
+    char* out2;
 };
 
 constexpr int kMaxPacked = 256;   // sequences whose counts a workgroup scans
@@ -84,6 +90,7 @@ bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream);
 // another (n_qred gemm_reduce_blocks) behind it in the same launch.  False for
 // a shape that is not instantiated.
 bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream);
+bool launch_tile(const GemmPlan& p, const QkvGemmArgs& g, hipStream_t stream);
 bool launch_tile_swiglu(const GemmPlan& p, const GemmArgs& g, hipStream_t stream);
 bool launch_tile_qred(const GemmPlan& p, const GemmArgs& g, const GemmArgs& q, int n_qred, hipStream_t stream);
 

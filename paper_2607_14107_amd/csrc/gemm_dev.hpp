@@ -65,7 +65,13 @@ __device__ __forceinline__ char* out_ptr(const GemmArgs& g, int b, int pos, int 
         return g.out0 + (static_cast<size_t>(m) * g.N + n) * es;
     const size_t row = static_cast<size_t>(b) * g.seq + pos;
     if (n < g.n0) return g.out0 + (row * g.n0 + n) * es;
-    if (!g.w2) return g.out1 + (row * (g.N - g.n0) + (n - g.n0)) * es;
+    return g.out1 + (row * (g.N - g.n0) + (n - g.n0)) * es;
+}
+template <bool BF16>
+__device__ __forceinline__ char* out_ptr(const QkvGemmArgs& g, int b, int pos, int m, int n) {
+    constexpr size_t es = Elem<BF16>::kBytes;
+    const size_t row = static_cast<size_t>(b) * g.seq + pos;
+    if (n < g.n0) return g.out0 + (row * g.n0 + n) * es;
     if (n < g.n1) return g.out1 + (row * (g.n1 - g.n0) + (n - g.n0)) * es;
     return g.out2 + (static_cast<size_t>(m) * (g.N - g.n1) + (n - g.n1)) * es;
 }
@@ -88,7 +94,12 @@ __device__ __forceinline__ void store8(char* dst, const float* v) {
 __device__ __forceinline__ const char* weight_row(const GemmArgs& g, int n, int es) {
     if (n >= g.N) return nullptr;
     if (n < g.n0) return g.w0 + static_cast<size_t>(n) * g.K * es;
-    if (g.w2 && n >= g.n1) return g.w2 + static_cast<size_t>(n - g.n1) * g.K * es;
+    return g.w1 + static_cast<size_t>(n - g.n0) * g.K * es;
+}
+__device__ __forceinline__ const char* weight_row(const QkvGemmArgs& g, int n, int es) {
+    if (n >= g.N) return nullptr;
+    if (n < g.n0) return g.w0 + static_cast<size_t>(n) * g.K * es;
+    if (n >= g.n1) return g.w2 + static_cast<size_t>(n - g.n1) * g.K * es;
     return g.w1 + static_cast<size_t>(n - g.n0) * g.K * es;
 }
 
@@ -97,8 +108,8 @@ __device__ __forceinline__ const char* weight_row(const GemmArgs& g, int n, int 
 // waves take super-steps w, w+4, w+8, ... of K and are summed in LDS.
 // ---------------------------------------------------------------------------
 
-template <bool BF16, int MT>
-__device__ __forceinline__ void small_body(const GemmArgs& g, int bx, int by) {
+template <bool BF16, int MT, class G>
+__device__ __forceinline__ void small_body(const G& g, int bx, int by) {
     using T = Elem<BF16>;
     constexpr int ES = T::kBytes;
     constexpr int BM = MT * 16;
@@ -246,8 +257,8 @@ __device__ __forceinline__ int dma_swz(int r, int c) { return r * kDmaStage + ((
 // global -> LDS transfers (below); taken for row tiles of at most 64 rows,
 // where it made the batch-1 Q projection 13.8 -> 13.3 us, while the 144- and
 // 160-row refreshes ran 27.5 -> 31.1 and 25.4 -> 28.0 us with it.
-template <bool BF16, int MT, int NST, int NS = 4, bool NTW = false, bool REG = (MT <= 4)>
-__device__ __forceinline__ void dma_body(const GemmArgs& g, int blk) {
+template <bool BF16, int MT, int NST, int NS = 4, bool NTW = false, bool REG = (MT <= 4), class G>
+__device__ __forceinline__ void dma_body(const G& g, int blk) {
     static_assert(NS == 3 || NS == 4, "three or four LDS slots");
     using T = Elem<BF16>;
     constexpr int ES = T::kBytes;
@@ -564,8 +575,8 @@ __device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, 
 // pair.  Unsplit, dense rows, F a multiple of 16.  gate and up are rounded to
 // bf16 first, as the separate product stores them, and silu_mul is the separate
 // pass's: the same bits as that product and that pass.
-template <int MI, int NJ, bool SWI = false>
-__device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
+template <int MI, int NJ, bool SWI = false, class G>
+__device__ __forceinline__ void tile_body(const G& g, int blk) {
     static_assert(MI % 2 == 0 && MI >= 2 && MI <= 8 && NJ >= 2 && NJ <= 4, "64 to 256 rows, 128 to 256 columns");
     constexpr int ES = 2;                                // bf16 operands
     constexpr int BM = 32 * MI, BN = 64 * NJ;
@@ -878,8 +889,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int blk) {
 // Split-K reduction: thread = (column tile, row, 8 columns); sums the splits
 // in order and stores the row through the published row map.  `id` counts the
 // threads of the whole reduction (gemm_reduce_blocks workgroups of kGemmBlock).
-template <bool BF16>
-__device__ __forceinline__ void reduce_body(const GemmArgs& g, long id) {
+template <bool BF16, class G>
+__device__ __forceinline__ void reduce_body(const G& g, long id) {
     const long per_tile = static_cast<long>(g.m_max) * 16;
     const int ct = static_cast<int>(id / per_tile);
     if (ct >= g.col_tiles) return;

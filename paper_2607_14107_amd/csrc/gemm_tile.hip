@@ -9,8 +9,8 @@
 namespace ps {
 namespace {
 
-template <int MI, int NJ>
-__global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(GemmArgs g) {
+template <int MI, int NJ, class G>
+__global__ __launch_bounds__(kTileThreads) void gemm_tile_kernel(G g) {
     tile_body<MI, NJ>(g, blockIdx.x);
 }
 
@@ -41,18 +41,22 @@ __global__ __launch_bounds__(kTileThreads) void tile_qred_kernel(TileQArgs k) {
     reduce_body<true>(k.q, static_cast<long>(blockIdx.x - k.n_tile) * kTileThreads + threadIdx.x);
 }
 
-}  // namespace
-
-bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream) {
+template <class G>
+bool launch_tile_of(const GemmPlan& p, const G& g, hipStream_t stream) {
     const dim3 grid(p.grid), block(kTileThreads);
     switch (10 * p.tile_mi + p.tile_nj) {
 #define PS_CASE(MI, NJ) \
-        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_tile_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
+        case 10 * MI + NJ: hipLaunchKernelGGL((gemm_tile_kernel<MI, NJ, G>), grid, block, 0, stream, g); return true;
         PS_TILE_SHAPES(PS_CASE)
 #undef PS_CASE
         default: return false;
     }
 }
+
+}  // namespace
+
+bool launch_tile(const GemmPlan& p, const GemmArgs& g, hipStream_t stream) { return launch_tile_of(p, g, stream); }
+bool launch_tile(const GemmPlan& p, const QkvGemmArgs& g, hipStream_t stream) { return launch_tile_of(p, g, stream); }
 
 bool launch_tile_swiglu(const GemmPlan& p, const GemmArgs& g, hipStream_t stream) {
     const dim3 grid(p.grid), block(kTileThreads);
