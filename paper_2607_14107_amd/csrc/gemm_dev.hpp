@@ -779,14 +779,9 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
                 PS_TILE_STEP(kt + 3, sa3, sb3, sa0, sb0)
             }
         }
-        if (kt < nkt) {                                  // what is left of a split that NS does not divide
+        if (kt < nkt) {                                  // one or two steps are left (two of an even split in fours)
             PS_TILE_STEP(kt, sa0, sb0, sa1, sb1)
-            if (kt + 1 < nkt) {
-                PS_TILE_STEP(kt + 1, sa1, sb1, sa2, sb2)
-                if constexpr (NS > 3) {
-                    if (kt + 2 < nkt) PS_TILE_STEP(kt + 2, sa2, sb2, sa3, sb3)
-                }
-            }
+            if (NS == 4 || kt + 1 < nkt) PS_TILE_STEP(kt + 1, sa1, sb1, sa2, sb2)
         }
 #undef PS_TILE_STEP
     }
