@@ -42,17 +42,19 @@ typedef float float2_hw __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2_hw){lo, hi}, bf16x2_hw));
 }
-// Four floats to packed bf16 with pack_bf16x2's bits, NaN too: two compares in
-// the usual case, the selects only where a lane of the wave holds a NaN.
-__device__ __forceinline__ uint2 cvt4_bf16(float a, float b, float c, float d) {
-    if (__builtin_amdgcn_ballot_w64(__builtin_isunordered(a, b) || __builtin_isunordered(c, d))) {
-        const float nan = __uint_as_float(0x7fc00000u);
-        a = a == a ? a : nan;
-        b = b == b ? b : nan;
-        c = c == c ? c : nan;
-        d = d == d ? d : nan;
-    }
-    return make_uint2(cvt_pk_bf16(a, b), cvt_pk_bf16(c, d));
+// Four bf16 that cvt_pk_bf16 made: a NaN becomes 0x7fc0, as from pack_bf16x2.
+__device__ __forceinline__ void quiet_bf16x4(uint2* p) {
+    auto quiet = [](uint32_t w) {
+        if ((w & 0x7fffu) > 0x7f80u) w = (w & 0xffff0000u) | 0x7fc0u;
+        if ((w & 0x7fff0000u) > 0x7f800000u) w = (w & 0xffffu) | 0x7fc00000u;
+        return w;
+    };
+    *p = make_uint2(quiet(p->x), quiet(p->y));
+}
+// The values that four floats have after a rounding to bf16 (NaN stays NaN).
+__device__ __forceinline__ floatx4 round_bf16(const floatx4& v) {
+    const uint32_t a = cvt_pk_bf16(v[0], v[1]), b = cvt_pk_bf16(v[2], v[3]);
+    return floatx4{bf16_lo(a), bf16_hi(a), bf16_lo(b), bf16_hi(b)};
 }
 
 // Storage traits: E = element count of one 16-byte chunk.

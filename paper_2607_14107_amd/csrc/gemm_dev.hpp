@@ -798,21 +798,26 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
         const int F = g.N / 2, f0 = n0 / 2 + 16 * NP * wn;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
+            bool nan = false;
 #pragma unroll
             for (int i = 0; i < HA; ++i)
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
+                    const floatx4 gt = round_bf16(acc[HA * hh + i][j]), up = round_bf16(acc[HA * hh + i][j + NP]);
                     float v[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float gt = bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j][e], 0.f)));
-                        const float up =
-                            bf16_to_f32(static_cast<uint16_t>(cvt_pk_bf16(acc[HA * hh + i][j + NP][e], 0.f)));
-                        v[e] = silu_mul(gt, up);
-                    }
+                    for (int e = 0; e < 4; ++e) v[e] = silu_mul(gt[e], up[e]);
+                    nan |= __builtin_isunordered(v[0], v[1]) || __builtin_isunordered(v[2], v[3]);
                     *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
-                        cvt4_bf16(v[0], v[1], v[2], v[3]);
+                        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
                 }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+#pragma unroll
+                for (int i = 0; i < HA; ++i)
+#pragma unroll
+                    for (int j = 0; j < NP; ++j)
+                        quiet_bf16x4(reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg));
+            }
             __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -854,16 +859,34 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
     constexpr int CPR = 2 * NJ;                          // 16-byte chunks of a row
     static_assert(2 * ER * EP <= BM * kTileStage && 2 * ER * EP <= BN * kTileStage, "two waves' rows fit a slot");
     char* ep = (w < 2 ? sa0 : w < 4 ? sa1 : w < 6 ? sb0 : sb1) + (w & 1) * ER * EP;
+    // NaNs become 0x7fc0, as from the other kernels: the rows are staged by
+    // cvt_pk_bf16, looked through for NaNs while those LDS writes are under way,
+    // and changed in LDS where the wave holds one.  (A branch every four values
+    // made the batch-8 step 2.6 us of 215 slower.)
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
+        bool nan = false;
 #pragma unroll
         for (int i = 0; i < HA; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const floatx4 v = acc[HA * hh + i][j];
                 *reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg) =
-                    cvt4_bf16(v[0], v[1], v[2], v[3]);
+                    make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
             }
+#pragma unroll
+        for (int i = HA * hh; i < HA * (hh + 1); ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                nan |= __builtin_isunordered(acc[i][j][0], acc[i][j][1]) ||
+                       __builtin_isunordered(acc[i][j][2], acc[i][j][3]);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+#pragma unroll
+            for (int i = 0; i < HA; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    quiet_bf16x4(reinterpret_cast<uint2*>(ep + (16 * i + fr) * EP + 32 * j + 8 * kg));
+        }
         __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
