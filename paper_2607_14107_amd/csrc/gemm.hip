@@ -143,27 +143,31 @@ static int quoted_split(bool bf16, long m_max, int N, int K) {
 // Estimated time (us) of the tile kernel with `tiles` tiles of 32 mi x 64 nj in
 // ks splits of `steps` K tiles: ceil(tiles * ks / 256) rounds of one workgroup
 // per CU, each a fixed cost (launch, row map, first DMA, stores) and its K
-// tiles at the shape's time, measured with every CU busy (12288 x 8192 x
-// 4096; 256 x 192 tiles 512 x 24576 x 4096); a split run adds the reduction's launch and its fp32 partials
-// written and read back (512 x 4096 x 4096 in 2 and 4 splits, 512 x 4096 x
-// 12288 in 4 and 8).
+// tiles at the shape's time; a split run adds the reduction's launch and its
+// fp32 partials written and read back (per MB).  The constants are a least
+// squares fit to the times of every plan within a third of the best one, for
+// 275 shapes of 65 to 4096 rows, 64 to 32768 columns and K 256 to 12288 (the
+// layers' products and others over those ranges, weights not cached).  Over 943
+// such shapes the plan that they choose is 0.7% slower than the fastest one in
+// the geometric mean, 5% at the 95th percentile and 20% at most; each shape's
+// time with every CU busy and partials at 0.32 us per MB: 1.5, 12 and 38%.
 static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_max, int N) {
     double kt = 0.0;
     switch (10 * mi + nj) {
-        case 84: kt = 1.52; break;
-        case 83: kt = 1.40; break;
-        case 64: kt = 1.27; break;
-        case 82: kt = 0.87; break;
-        case 44: kt = 0.89; break;
-        case 63: kt = 0.93; break;
-        case 62: kt = 0.67; break;
-        case 43: kt = 0.71; break;
-        case 42: kt = 0.53; break;
-        case 24: kt = 0.70; break;
-        default: kt = 0.42; break;
+        case 84: kt = 1.49; break;
+        case 83: kt = 1.29; break;
+        case 64: kt = 1.25; break;
+        case 82: kt = 0.80; break;
+        case 44: kt = 0.86; break;
+        case 63: kt = 0.87; break;
+        case 62: kt = 0.62; break;
+        case 43: kt = 0.73; break;
+        case 42: kt = 0.52; break;
+        case 24: kt = 0.69; break;
+        default: kt = 0.36; break;
     }
     const double rounds = static_cast<double>((tiles * ks + kTargetWgs - 1) / kTargetWgs);
-    return rounds * (steps * kt + 4.0) + (ks > 1 ? 5.0 + 4.0 * ks * m_max * N * 0.32e-6 : 0.0);
+    return rounds * (steps * kt + 4.0) + (ks > 1 ? 4.0 + 4.0 * ks * m_max * N * 0.4e-6 : 0.0);
 }
 
 // The tile kernel's plan: the tile shape and split with the least estimated
@@ -339,8 +343,8 @@ static double plan_cost(const GemmPlan& p, long m, int N) {
 }
 
 // The SwiGLU form's plan, false where two calls are faster (or the only way).
-// It runs where the product's plan is unsplit, in the cheapest tile shape that
-// pairs gate and up columns, when its estimate and its longer epilogue (expf
+// It runs unsplit, in the cheapest tile shape that pairs gate and up columns,
+// when its estimate and its longer epilogue (expf
 // and a division per pair: 5.5 us for a round of 256 x 256 tiles, by the pairs
 // of a lane for smaller ones) are no more above the product's own plan than the
 // separate pass costs (6.5 us for its launch and the wait behind the product,
@@ -350,8 +354,10 @@ static double plan_cost(const GemmPlan& p, long m, int N) {
 // and the pass: 94.2 against 90.5 us repeated alone, but two layers and the head
 // of a forward 1106.6 against 1109.3 us.
 static bool swiglu_plan(const GemmPlan& plan, long m_max, int N, int K, GemmPlan& p) {
-    if (!plan.tile || plan.ksplit > 1 || N % 32 != 0) return false;
+    if (!plan.tile || N % 32 != 0) return false;
     p = plan;
+    p.ksplit = 1;
+    p.steps_per_split = K / 64;
     const int nkt = K / 64;
     double best = 1e30;
 #define PS_CASE(MI, NJ)                                                                                          \

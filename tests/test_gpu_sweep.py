@@ -33,6 +33,13 @@ def P():
     return polestar
 
 
+def _plan(P, m, N, K):
+    """The bf16 product's kernel (0 small, 1 DMA, 2 tile, 3 rows), tile rows and columns, splits of K."""
+    info = (ctypes.c_int * 4)()
+    P.lib().ps_gemm_plan_info(1, ctypes.c_long(m), N, K, info)
+    return tuple(info)
+
+
 def _i32(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
@@ -99,11 +106,11 @@ def _gemm_dims(g, dtype):
     return d, hd
 
 
-@pytest.mark.parametrize("case", range(12))
+@pytest.mark.parametrize("case", range(18))
 def test_linear_random_tile_shapes(P, case):
-    """Row counts and widths where the tile kernel's plans compete (256- or
-    192-row by 256- or 192-column tiles, unsplit or split K), ragged in both
-    directions, bf16."""
+    """Row counts and widths where the tile kernel's plans compete (64- to
+    256-row by 128-column tiles, unsplit; the last six few rows of a long K,
+    which plans split), ragged in both directions, bf16."""
     torch = pytest.importorskip("torch")
     g = np.random.default_rng(17000 + case)
     batch = int(g.integers(1, 4))
@@ -112,6 +119,13 @@ def test_linear_random_tile_shapes(P, case):
     seq = n + rs + int(g.integers(0, 30))
     K = int(g.choice([1024, 2048, 3072, 4096]))
     N = 16 * int(g.integers(16, 376))                      # 256 .. 6000 columns
+    if case >= 12:
+        n = int(g.integers(66, 300)) // batch
+        seq = n + rs + int(g.integers(0, 30))
+        K = 128 * int(g.integers(20, 64))
+        N = 16 * int(g.integers(4, 120))                   # 64 .. 1900 columns
+    kernel, _, _, splits = _plan(P, batch * n, N, K)
+    assert kernel == 2 and (splits > 1) == (case >= 12)
     x = inputs.store(g.standard_normal((batch, seq, K)).astype(np.float32), "bf16")
     w = inputs.store((g.standard_normal((N, K)) * 0.05).astype(np.float32), "bf16")
     y = torch.empty((batch, n, N), dtype=torch.bfloat16, device="cuda")
@@ -121,23 +135,32 @@ def test_linear_random_tile_shapes(P, case):
                       f"linear {batch}x{n} rows x {N} x K {K}")
 
 
-@pytest.mark.parametrize("m,N,K", [
-    # each tile shape (rows x columns) of the tile kernel, K tiles per split whole and not whole
-    # multiples of its LDS slots, ragged last tiles in both directions
-    (66, 80, 256), (70, 64, 384), (98, 64, 1536), (71, 96, 1664), (69, 64, 4352),             # 64 x 128
-    (385, 4656, 256), (262, 6544, 384), (68, 4288, 2048), (66, 2432, 3968),                   # 128 x 128
-    (771, 6624, 256), (775, 6576, 512), (391, 2704, 2944), (69, 6864, 3840),                  # 128 x 192
-    (1055, 6576, 384), (1032, 6672, 512), (257, 4288, 3200),                                  # 128 x 256
-    (523, 6624, 384), (527, 6624, 256), (133, 5456, 3328), (137, 2816, 3328),                 # 192 x 128
-    (1031, 7232, 384), (1032, 7312, 256), (269, 4384, 3200),                                  # 192 x 192
-    (772, 7104, 384), (774, 6928, 256), (193, 6368, 4608),                                    # 256 x 128
-    (1156, 6976, 256), (2048, 6144, 1024), (1537, 8192, 512), (2305, 7696, 384),              # 256 x 192, 192 x 256, 256 x 256
+@pytest.mark.parametrize("m,N,K,rows,cols,splits", [
+    # each tile shape (rows x columns) of the tile kernel, unsplit and split where plans take both, K tiles
+    # per split whole and not whole multiples of its LDS slots, ragged last tiles in both directions
+    (66, 80, 256, 64, 128, 1), (70, 64, 384, 64, 128, 1), (257, 4288, 3200, 64, 128, 1),
+    (98, 64, 1536, 64, 128, 3), (71, 96, 1664, 64, 128, 4), (69, 64, 4352, 64, 128, 7),
+    (385, 4656, 256, 128, 128, 1), (262, 6544, 384, 128, 128, 1),
+    (68, 4288, 2048, 64, 128, 3), (66, 2432, 3968, 64, 128, 6), (66, 4448, 2816, 128, 128, 6), (2713, 64, 3968, 128, 128, 8),
+    (771, 6624, 256, 128, 192, 1), (775, 6576, 512, 128, 192, 1), (74, 6768, 5376, 128, 192, 7),
+    (71, 8352, 3200, 128, 192, 5),
+    (1055, 6576, 384, 128, 256, 1), (1032, 6672, 512, 128, 256, 1), (69, 12400, 5120, 128, 256, 5),
+    (523, 6624, 384, 192, 128, 1), (527, 6624, 256, 192, 128, 1), (133, 5456, 3328, 192, 128, 5),
+    (130, 4112, 3584, 192, 128, 7),
+    (1031, 7232, 384, 192, 192, 1), (1032, 7312, 256, 192, 192, 1), (142, 11408, 4096, 192, 192, 4),
+    (1156, 6976, 256, 192, 256, 1), (2305, 7696, 384, 192, 256, 1), (259, 6288, 11520, 192, 256, 5),
+    (772, 7104, 384, 256, 128, 1), (774, 6928, 256, 256, 128, 1), (195, 8240, 4096, 256, 128, 3),
+    (2048, 6144, 1024, 256, 192, 1), (1737, 6608, 128, 256, 192, 1), (195, 10992, 11648, 256, 192, 4),
+    (1537, 8192, 512, 256, 256, 1), (1546, 7344, 128, 256, 256, 1), (405, 4112, 11648, 256, 256, 7),
 ])
-def test_linear_tile_kernel_edges(P, m, N, K):
+def test_linear_tile_kernel_edges(P, m, N, K, rows, cols, splits):
     """The tile kernel's shapes at their edges against an fp32 product of the
     same bf16 operands: both sum exact products in fp32 in some order and
     round once, so a row's largest difference is one bf16 step (2^-8) of the
-    row's largest value plus fp32 noise, well under the 2e-2 of the sweep."""
+    row's largest value plus fp32 noise, well under the 2e-2 of the sweep.  The
+    plan is named, so that a change of the plan's rule cannot move a case to
+    another kernel unseen."""
+    assert _plan(P, m, N, K) == (2, rows, cols, splits)
     torch = pytest.importorskip("torch")
     gen = torch.Generator(device="cuda").manual_seed(m * 7 + N)
     x = torch.randn((1, m + 3, K), generator=gen, device="cuda").to(torch.bfloat16)
@@ -349,15 +372,13 @@ def test_linear_swiglu_has_its_calls_values(P, n, d, ffn, tile):
 
 @pytest.mark.parametrize("m,N,K,kernel", [
     (9, 256, 256, (0, 0, 0, 1)), (40, 4096, 4096, (1, 0, 0, 8)),
-    (529, 6560, 128, (2, 192, 128, 1)), (1546, 7232, 128, (2, 256, 256, 1)), (68, 4288, 2048, (2, 128, 128, 4)),
+    (529, 6560, 128, (2, 192, 128, 1)), (1546, 7232, 128, (2, 256, 256, 1)), (68, 4288, 2048, (2, 64, 128, 3)),
 ])
 def test_linear_nan_bits(P, m, N, K, kernel):
     """A NaN output is the quiet NaN 0x7fc0 from every kernel, whatever the
     sign and payload of the operands', and reaches its own row only."""
     torch = pytest.importorskip("torch")
-    info = (ctypes.c_int * 4)()
-    P.lib().ps_gemm_plan_info(1, ctypes.c_long(m), N, K, info)
-    assert tuple(info) == kernel
+    assert _plan(P, m, N, K) == kernel
     gen = torch.Generator(device="cuda").manual_seed(m)
     x = torch.randn((1, m, K), generator=gen, device="cuda").to(torch.bfloat16)
     w = torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16)
