@@ -266,18 +266,28 @@ GemmPlan gemm_plan(bool bf16, long m_max, int N, int K) {
     }
     // bf16 above that: the tile kernel, but for two ranges that the DMA kernel
     // runs in one round:
-    // - 65 to 160 rows (one row tile) of at least 64 MB of weights, whose
-    //   stream it marks non-temporal: a batch-1 LLaDA-8B layer (138 x 8192 x
-    //   4096) on weights that are not cached 21.5 us against 23.8 for the tile
-    //   kernel, and the kernels after it find more of theirs in the caches
-    //   (57.5 against 61.8 us per layer step); smaller weights are 5-25%
-    //   faster on the tile kernel (160 x 4096 x 4096: 24.3 against 18.7 us);
+    // - one row tile of 65 to 160 rows whose weights are a round's worth of its
+    //   longest splits (60 MB and K >= 4096, or 56 MB up to 96 rows); it marks
+    //   their stream non-temporal.  Against the tile kernel on weights that are
+    //   not cached, 66 / 96 / 138 / 160 rows: 8192 x 4096 0.82 0.83 0.84 0.88 of
+    //   its time, 7680 x 4096 0.82 0.88 0.92 0.96, 4480 x 7168 0.85 0.93 0.95
+    //   0.95, 3840 x 8192 0.80 0.83 0.87 0.89, 5376 x 6144 0.85 0.97 0.98 1.0,
+    //   8192 x 3584 0.85 0.91 0.98 1.08 (128 rows 0.92 to 1.13, 3584: 1.28); less
+    //   than that, 6144 x 4096 0.99 1.05 1.10 1.09, 5632 x 5120 0.99 1.06 1.09
+    //   1.05, 3072 x 8192 0.97 1.06 1.07 1.06; shorter K, 10880 x 3072 0.86 0.99
+    //   1.18 1.13, 16384 x 2048 1.08 1.13 1.10 1.12, 32768 x 1024 0.83 0.90 0.98
+    //   1.04.  The kernels behind it also find more of theirs in the caches (a
+    //   batch-1 LLaDA-8B step 57.5 against 61.8 us);
     // - 161 to 256 rows of K >= 1536 in two row tiles (4096 x 4096: 176 rows
     //   20.3 against 24.2 us, 224 rows 22.7 / 25.5, 256 rows 27.2 / 26.1; with
-    //   K = 1024 and below the tile kernel is 10-45% faster).
+    //   K = 1024 and below the tile kernel is 10-45% faster; for narrower weights
+    //   it is by itself up to 30% faster at longer K too, but the fused step
+    //   takes these Q projections into its select launch from the DMA kernel).
     if (bf16) {
-        const bool dma_rows = m_max <= 160 ? m_max > 64 && static_cast<long>(N) * K >= 1L << 25
-                                           : m_max <= 256 && K >= 1536;
+        const long weights = static_cast<long>(N) * K;
+        const bool dma_rows = m_max <= 96    ? m_max > 64 && weights >= 28L << 20
+                              : m_max <= 160 ? K >= 4096 && weights >= 30L << 20
+                                             : m_max <= 256 && K >= 1536;
         if (!(dma_rows && plan_dma(p, m_max, N, K, quoted))) plan_tile(p, m_max, N, K, quoted);
         return p;
     }

@@ -315,3 +315,21 @@ def test_binding_fails_loudly_without_gpu_tensors():
     x = torch.zeros(1, 4, 8)
     with pytest.raises(ValueError):
         ps.drift(x, x)
+
+
+def test_dma_plan_line(L):
+    """Up to 160 rows go to the DMA kernel (1) from the weights' size on where it
+    is the faster one, on either side of any single layer's shape, and to the
+    tile kernel (2) for shorter K."""
+    def kernel(m, n, k):
+        out = (ctypes.c_int * 4)()
+        L.ps_gemm_plan_info(1, ctypes.c_long(m), n, k, out)
+        return out[0]
+    for n, k in [(8192, 4096), (8064, 4096), (7680, 4096), (4480, 7168), (3840, 8192), (4096, 8192)]:
+        assert kernel(66, n, k) == kernel(138, n, k) == kernel(160, n, k) == 1, (n, k)
+    for n, k in [(8192, 3584), (7168, 4096)]:
+        assert kernel(96, n, k) == 1 and kernel(97, n, k) == 2, (n, k)
+    for n, k in [(16384, 2048), (10880, 3072)]:
+        assert kernel(97, n, k) == kernel(160, n, k) == 2, (n, k)
+    for n, k in [(6144, 4096), (4096, 4096), (24576, 1024)]:
+        assert kernel(66, n, k) == kernel(160, n, k) == 2, (n, k)
