@@ -399,25 +399,51 @@ polestar_status gemm_run(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t s
     return run_plan(bf16, p, g, stream, deferred);
 }
 
-// Half the capacity is the line because a packet holds the members of half the
-// clusters (16 lists of 96 entries, 47 used, 8192 x 4096: unpacked 82 us,
-// packed in the plan of 768 rows and the other plan's empty launch 57 us);
-// a launch that returns at once takes 4.5 us, priced at 4.
+// The packed form of a refresh whose unpacked plan is `plan`, false where it has
+// none: its larger shape must be no slower than the plan's (2%: lists may be
+// full), and half-full lists, the usual packet (the members of half the
+// clusters), must gain more than the 2 us that the running sum of the counts
+// takes.  rows_small goes on past half as far as the smaller shape's estimate is
+// below the larger one's.  8192 x 4096 weights, lists of 96 entries, unpacked
+// and packed, with uneven counts: 16 lists 45% full 83.7 and 48.4 us, 50% 84.9 /
+// 51.9, 52% (the first past the line) 81.9 / 83.7, 65% 82.3 / 83.4, 80% 84.6 /
+// 85.0, 100% 86.7 / 90.2; 12 lists 50% 78.3 / 49.5, 65% 80.6 / 51.1, 80% 81.0 /
+// 83.3, 100% 85.8 / 86.6; 8 lists 50% 44.3 / 43.9, 100% 51.6 / 52.8.  In a
+// denoising loop (16 sequences, 6 layers of 2048 channels, half of 8 clusters
+// refreshed) the lists were 0.21 to 0.73 full, 0.49 in the median, and at most
+// half in 54 to 61% of the packets.
+static bool packed_plan(const GemmPlan& plan, long m_max, int N, int K, PackedPlan& q) {
+    const int nkt = K / 64;
+    const double now = plan_cost(plan, m_max, N);
+    double best = now - 2.0;
+    auto cost = [&](int mi, int nj, long row_tiles) {
+        return tile_cost(mi, nj, row_tiles * ceil_div(N, 64 * nj), 1, nkt, m_max, N);
+    };
+#define PS_CASE(MI, NJ, SMI, SNJ)                                                                                     \
+    {                                                                                                                 \
+        const long full_tiles = ceil_div(m_max, 32 * MI), half_tiles = ceil_div(ceil_div(m_max, 2), 32 * SMI);        \
+        const double full = cost(MI, NJ, full_tiles), half = cost(SMI, SNJ, half_tiles);                              \
+        if (full <= 1.02 * now && half < best) {                                                                      \
+            best = half;                                                                                              \
+            long rt = half_tiles;                                                                                     \
+            while (rt * 32 * SMI < m_max && cost(SMI, SNJ, rt + 1) < full) ++rt;                                      \
+            const long grid = std::max(full_tiles * ceil_div(N, 64 * NJ), rt * ceil_div(N, 64 * SNJ));                \
+            q = {MI, NJ, SMI, SNJ, static_cast<int>(rt * 32 * SMI), static_cast<int>(grid)};                          \
+        }                                                                                                             \
+    }
+    PS_PACKED_PAIRS(PS_CASE)
+#undef PS_CASE
+    return best < now - 2.0;
+}
+
 polestar_status gemm_run_refresh(bool bf16, const GemmPlan& p, GemmArgs g, hipStream_t stream) {
-    if (!bf16 || !p.tile || p.ksplit > 1 || g.block_len > 0 || g.k_max == 0 || g.batch > kMaxPacked)
+    PackedPlan q;
+    if (!bf16 || !p.tile || p.ksplit > 1 || g.block_len > 0 || g.k_max == 0 || g.batch > kMaxPacked ||
+        !packed_plan(p, g.m_max, g.N, g.K, q))
         return gemm_run(bf16, p, g, stream);
-    const int half = ceil_div(g.m_max, 2);
-    const GemmPlan q = gemm_plan(bf16, half, g.N, g.K);
-    if (!q.tile || q.ksplit > 1 || plan_cost(q, half, g.N) + 4.0 > plan_cost(p, g.m_max, g.N))
-        return gemm_run(bf16, p, g, stream);
-    g.packed = 1;
-    g.rows_lo = 0;
-    g.rows_hi = half;
-    const polestar_status st = gemm_run(bf16, q, g, stream);
-    if (st != POLESTAR_OK) return st;
-    g.rows_lo = half;
-    g.rows_hi = g.m_max;
-    return gemm_run(bf16, p, g, stream);
+    gemm_finalize_args(p, g);
+    if (!launch_packed(q, g, stream)) return POLESTAR_ERR_UNSUPPORTED;
+    return launch_status();
 }
 
 }  // namespace ps
@@ -434,6 +460,18 @@ static void plan_info(const ps::GemmPlan& p, int* out) {
 
 extern "C" void ps_gemm_plan_info(int bf16, long m, int N, int K, int* out) {
     plan_info(ps::gemm_plan(bf16 != 0, m, N, K), out);
+}
+
+// The packed refresh of that product: rows and columns of the larger and the
+// smaller tile, the rows up to which the smaller one runs; 0 where the rows
+// are not packed.
+extern "C" int ps_packed_plan_info(long m, int N, int K, int* out) {
+    const ps::GemmPlan p = ps::gemm_plan(true, m, N, K);
+    ps::PackedPlan q;
+    if (!p.tile || p.ksplit > 1 || !ps::packed_plan(p, m, N, K, q)) return 0;
+    const int v[5] = {32 * q.mi, 64 * q.nj, 32 * q.small_mi, 64 * q.small_nj, q.rows_small};
+    std::copy(v, v + 5, out);
+    return 1;
 }
 
 // The same for the one-launch SwiGLU product of N = 2 ffn columns; 0 where

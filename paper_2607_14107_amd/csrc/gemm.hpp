@@ -34,10 +34,6 @@ struct GemmArgs {
     int ksplit;
     int steps_per_split;   // 256-byte super-steps per split (tile kernel: 128-byte K tiles)
     int row_tiles, col_tiles;
-    // Packed rows (refresh mode without a block, batch <= kMaxPacked, tile
-    // kernel, unsplit): the lists' used entries alone, one sequence after the
-    // other, and the launch returns unless rows_lo < their number <= rows_hi.
-    int packed, rows_lo, rows_hi;
 };
 
 // Three weight matrices (refresh mode without lists): w1 up to column n1 (v_cache
@@ -50,7 +46,7 @@ struct QkvGemmArgs : GemmArgs {
     char* out2;
 };
 
-constexpr int kMaxPacked = 256;   // sequences whose counts a workgroup scans
+constexpr int kMaxPacked = 256;   // most sequences of a packed refresh
 
 struct GemmPlan {
     bool small;         // gemm_small_kernel (<= 64 rows) instead of gemm_rows_kernel
@@ -94,9 +90,18 @@ bool launch_tile(const GemmPlan& p, const QkvGemmArgs& g, hipStream_t stream);
 bool launch_tile_swiglu(const GemmPlan& p, const GemmArgs& g, hipStream_t stream);
 bool launch_tile_qred(const GemmPlan& p, const GemmArgs& g, const GemmArgs& q, int n_qred, hipStream_t stream);
 
+// A packed refresh: the tile shape for full lists, the one for at most
+// rows_small rows, and the workgroups that either needs.
+struct PackedPlan {
+    int mi, nj, small_mi, small_nj;
+    int rows_small;
+    int grid;
+};
+bool launch_packed(const PackedPlan& p, const GemmArgs& g, hipStream_t stream);
+
 // gemm_run of a refresh (refresh_gemm_args).  Lists without a block are update
 // packets, sized for the whole window and usually about half full: their used
-// rows are packed, and the plan for half the capacity runs where they fit it.
+// rows alone run, in smaller tiles where they are few enough.
 polestar_status gemm_run_refresh(bool bf16, const GemmPlan& plan, GemmArgs g, hipStream_t stream);
 
 // Arguments of the K/V refresh GEMM (polestar_refresh_kv's, after its checks):

@@ -529,39 +529,77 @@ __device__ __forceinline__ bool tile_coords(const GemmArgs& g, int row_tiles, in
     return true;
 }
 
-// Packed rows: the running sum of the lists' counts (first[b] rows come before
-// sequence b's, first[batch] in all).  All kTileThreads threads.
-__device__ __forceinline__ void packed_rows(const GemmArgs& g, int* first) {
-    __shared__ int scratch[17];
-    const int t = threadIdx.x;
-    const int c = t < g.batch ? min(max(g.stale_count[t], 0), g.k_max) : 0;
+// What a tile's rows are: the plan's (map_row) ...
+template <class G>
+struct PlanRows {
+    const G& g;
+    __device__ __forceinline__ int tiles(int) const { return g.row_tiles; }
+    __device__ __forceinline__ void map(int m, int& b, int& pos) const { map_row(g, m, b, pos); }
+};
+
+// ... or packed: the lists' used entries alone (refresh mode without a block),
+// one sequence after the other.
+struct PackedRows {
+    const GemmArgs& g;
+    const int* first;      // [batch + 1] rows before each sequence's, and in all
     int total;
-    const int before = block_excl_scan(c, scratch, &total);
-    if (t <= kMaxPacked) first[t] = before;              // batch <= kMaxPacked
+    __device__ __forceinline__ int tiles(int bm) const { return (total + bm - 1) / bm; }
+    // b = -1 past the last row and for entries outside the sequence
+    __device__ __forceinline__ void map(int m, int& b, int& pos) const {
+        b = -1;
+        pos = 0;
+        if (m >= total) return;
+        int lo = 0, hi = g.batch;                        // first[lo] <= m < first[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (first[mid] <= m) lo = mid;
+            else hi = mid;
+        }
+        const int p = g.stale_idx[static_cast<size_t>(lo) * g.k_max + (m - first[lo])];
+        if (p < 0 || p >= g.seq) return;
+        b = lo;
+        pos = p;
+    }
+};
+
+// The running sum of the lists' counts into first[]; returns the total.  Every
+// wave scans (one load, no barrier between), the first one stores.
+__device__ __forceinline__ int packed_rows(const GemmArgs& g, int* first) {
+    const int lane = threadIdx.x & 63;
+    int total = 0;
+    for (int b0 = 0; b0 < g.batch; b0 += kWave) {
+        const int b = b0 + lane;
+        const int c = b < g.batch ? min(max(g.stale_count[b], 0), g.k_max) : 0;
+        const int incl = wave_incl_scan(c, lane);
+        if (threadIdx.x < kWave && b < g.batch) first[b] = total + incl - c;
+        total += __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    if (threadIdx.x == 0) first[g.batch] = total;
     __syncthreads();
+    return total;
 }
 
-// Packed row m -> (sequence, position); b = -1 past the last row and for
-// entries outside the sequence.
-__device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, int m, int& b, int& pos) {
-    b = -1;
-    pos = 0;
-    if (m >= first[g.batch]) return;
-    int lo = 0, hi = g.batch;                            // first[lo] <= m < first[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (first[mid] <= m) lo = mid;
-        else hi = mid;
-    }
-    const int p = g.stale_idx[static_cast<size_t>(lo) * g.k_max + (m - first[lo])];
-    if (p < 0 || p >= g.seq) return;
-    b = lo;
-    pos = p;
+// LDS slots per operand of a tile shape: as many as fit 150 KB, two to maxns.
+constexpr int tile_slots(int mi, int nj, int maxns = 4) {
+    const int slot = (32 * mi + 64 * nj) * kTileStage;
+    return maxns >= 4 && 4 * slot <= 150 * 1024 ? 4 : maxns >= 3 && 3 * slot <= 150 * 1024 ? 3 : 2;
 }
+
+// A workgroup's LDS: the slots (separate objects, so the compiler can tell them
+// apart) and its rows' sequences and positions.
+struct TileLds {
+    char *sa0, *sa1, *sa2, *sa3;
+    char *sb0, *sb1, *sb2, *sb3;
+    int *rowb, *rowp;
+};
 
 // The tile shapes (MI, NJ) that are instantiated.
 #define PS_TILE_SHAPES(X) X(8, 4) X(8, 3) X(8, 2) X(6, 4) X(6, 3) X(6, 2) X(4, 4) X(4, 3) X(4, 2) \
     X(2, 4) X(2, 2)
+
+// The pairs of a packed refresh: (MI, NJ) for full lists, (SMI, SNJ) for shorter
+// ones, in three slots at most and together within the LDS of a CU.
+#define PS_PACKED_PAIRS(X) X(6, 4, 6, 2) X(8, 2, 6, 2) X(8, 2, 4, 2) X(6, 2, 4, 2) X(4, 4, 4, 2)
 
 // The shapes of the SwiGLU form (an even number of column tiles per wave).
 #define PS_SWIGLU_SHAPES(X) X(8, 4) X(6, 4) X(4, 4) X(8, 2) X(6, 2) X(4, 2)
@@ -575,8 +613,8 @@ __device__ __forceinline__ void map_packed(const GemmArgs& g, const int* first, 
 // pair.  Unsplit, dense rows, F a multiple of 16.  gate and up are rounded to
 // bf16 first, as the separate product stores them, and silu_mul is the separate
 // pass's: the same bits as that product and that pass.
-template <int MI, int NJ, bool SWI = false, class G>
-__device__ __forceinline__ void tile_body(const G& g, int blk) {
+template <int MI, int NJ, bool SWI, int MAXNS, class G, class Rows>
+__device__ __forceinline__ void tile_run(const G& g, const Rows& rows, const TileLds& lds, int blk) {
     static_assert(MI % 2 == 0 && MI >= 2 && MI <= 8 && NJ >= 2 && NJ <= 4, "64 to 256 rows, 128 to 256 columns");
     constexpr int ES = 2;                                // bf16 operands
     constexpr int BM = 32 * MI, BN = 64 * NJ;
@@ -585,26 +623,21 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
     constexpr int HA = MI / 2;                           // row tiles of a half block
     constexpr int HB0 = (NJ + 1) / 2, HB1 = NJ / 2;      // column tiles of its two halves
     constexpr bool kQuad = MI * NJ >= 24;                // the whole step's fragments twice would not fit
-    // LDS slots: as many as fit 150 KB, two to four
-    constexpr int kSlot = (BM + BN) * kTileStage;
-    constexpr int NS = 4 * kSlot <= 150 * 1024 ? 4 : 3 * kSlot <= 150 * 1024 ? 3 : 2;
-    __shared__ __align__(16) char sa0[BM * kTileStage], sa1[BM * kTileStage];
-    __shared__ __align__(16) char sb0[BN * kTileStage], sb1[BN * kTileStage];
-    __shared__ __align__(16) char sa2[NS > 2 ? BM * kTileStage : 16], sa3[NS > 3 ? BM * kTileStage : 16];
-    __shared__ __align__(16) char sb2[NS > 2 ? BN * kTileStage : 16], sb3[NS > 3 ? BN * kTileStage : 16];
-    __shared__ int rowb[BM], rowp[BM];
-    __shared__ int first[kMaxPacked + 1];
+    constexpr int NS = tile_slots(MI, NJ, MAXNS);
+    char* const sa0 = lds.sa0;
+    char* const sa1 = lds.sa1;
+    char* const sa2 = lds.sa2;
+    char* const sa3 = lds.sa3;
+    char* const sb0 = lds.sb0;
+    char* const sb1 = lds.sb1;
+    char* const sb2 = lds.sb2;
+    char* const sb3 = lds.sb3;
+    int* const rowb = lds.rowb;
+    int* const rowp = lds.rowp;
 
     const int t = threadIdx.x;
-    int row_tiles = g.row_tiles;
-    if (g.packed) {
-        packed_rows(g, first);
-        const int total = first[g.batch];
-        if (total <= g.rows_lo || total > g.rows_hi) return;   // (uniform)
-        row_tiles = (total + BM - 1) / BM;
-    }
     int split, rt, ct;
-    if (!tile_coords(g, row_tiles, BN, blk, split, rt, ct)) return;
+    if (!tile_coords(g, rows.tiles(BM), BN, blk, split, rt, ct)) return;
     const int lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = w & 1, wn = w >> 1;
@@ -620,8 +653,7 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
     // each row tile publishes the map for the split-K reduction.
     int rb_ = -1, rp_ = 0;
     if (t < BM) {
-        if (g.packed) map_packed(g, first, m0 + t, rb_, rp_);
-        else map_row(g, m0 + t, rb_, rp_);
+        rows.map(m0 + t, rb_, rp_);
         rowb[t] = rb_;
         rowp[t] = rp_;
         if (g.ksplit > 1 && split == 0 && ct == 0 && m0 + t < g.m_max)
@@ -902,6 +934,35 @@ __device__ __forceinline__ void tile_body(const G& g, int blk) {
         __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
         __builtin_amdgcn_wave_barrier();
     }
+}
+
+template <int MI, int NJ, bool SWI = false, class G>
+__device__ __forceinline__ void tile_body(const G& g, int blk) {
+    constexpr int A = 32 * MI * kTileStage, B = 64 * NJ * kTileStage, NS = tile_slots(MI, NJ);
+    __shared__ __align__(16) char sa0[A], sa1[A], sa2[NS > 2 ? A : 16], sa3[NS > 3 ? A : 16];
+    __shared__ __align__(16) char sb0[B], sb1[B], sb2[NS > 2 ? B : 16], sb3[NS > 3 ? B : 16];
+    __shared__ int rowb[32 * MI], rowp[32 * MI];
+    const TileLds lds{sa0, sa1, sa2, sa3, sb0, sb1, sb2, sb3, rowb, rowp};
+    tile_run<MI, NJ, SWI, 4>(g, PlanRows<G>{g}, lds, blk);
+}
+
+// Packed rows in one of two tile shapes, in the same LDS: S* where the lists
+// hold at most rows_small rows, else the larger one, whose grid is launched
+// for full lists.
+template <int MI, int NJ, int SMI, int SNJ>
+__device__ __forceinline__ void packed_body(const GemmArgs& g, int rows_small, int blk) {
+    constexpr int A0 = 32 * MI * kTileStage, B0 = 64 * NJ * kTileStage, N0 = tile_slots(MI, NJ, 3);
+    constexpr int A1 = 32 * SMI * kTileStage, B1 = 64 * SNJ * kTileStage, N1 = tile_slots(SMI, SNJ, 3);
+    constexpr int A = A0 > A1 ? A0 : A1, B = B0 > B1 ? B0 : B1;
+    constexpr int A2 = N0 > 2 ? (N1 > 2 ? A : A0) : N1 > 2 ? A1 : 16, B2 = N0 > 2 ? (N1 > 2 ? B : B0) : N1 > 2 ? B1 : 16;
+    __shared__ __align__(16) char sa0[A], sa1[A], sa2[A2];
+    __shared__ __align__(16) char sb0[B], sb1[B], sb2[B2];
+    __shared__ int rowb[32 * (MI > SMI ? MI : SMI)], rowp[32 * (MI > SMI ? MI : SMI)];
+    __shared__ int first[kMaxPacked + 1];
+    const TileLds lds{sa0, sa1, sa2, sa2, sb0, sb1, sb2, sb2, rowb, rowp};
+    const PackedRows rows{g, first, packed_rows(g, first)};
+    if (rows.total <= rows_small) tile_run<SMI, SNJ, false, 3>(g, rows, lds, blk);
+    else tile_run<MI, NJ, false, 3>(g, rows, lds, blk);
 }
 
 // Split-K reduction: thread = (column tile, row, 8 columns); sums the splits

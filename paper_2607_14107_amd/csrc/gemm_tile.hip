@@ -19,6 +19,11 @@ __global__ __launch_bounds__(kTileThreads) void gemm_swiglu_kernel(GemmArgs g) {
     tile_body<MI, NJ, true>(g, blockIdx.x);
 }
 
+template <int MI, int NJ, int SMI, int SNJ>
+__global__ __launch_bounds__(kTileThreads) void gemm_packed_kernel(GemmArgs g, int rows_small) {
+    packed_body<MI, NJ, SMI, SNJ>(g, rows_small, blockIdx.x);
+}
+
 // refresh on the tile kernel, unsplit | Q split-K reduce: the tile
 // workgroups come first (tile_body's XCD-aware order counts from id 0), the
 // reduction's after them, on compute units the tiles leave free or as a short
@@ -64,6 +69,19 @@ bool launch_tile_swiglu(const GemmPlan& p, const GemmArgs& g, hipStream_t stream
 #define PS_CASE(MI, NJ) \
         case 10 * MI + NJ: hipLaunchKernelGGL((gemm_swiglu_kernel<MI, NJ>), grid, block, 0, stream, g); return true;
         PS_SWIGLU_SHAPES(PS_CASE)
+#undef PS_CASE
+        default: return false;
+    }
+}
+
+bool launch_packed(const PackedPlan& p, const GemmArgs& g, hipStream_t stream) {
+    const dim3 grid(p.grid), block(kTileThreads);
+    switch (1000 * p.mi + 100 * p.nj + 10 * p.small_mi + p.small_nj) {
+#define PS_CASE(MI, NJ, SMI, SNJ)                                                                             \
+        case 1000 * MI + 100 * NJ + 10 * SMI + SNJ:                                                           \
+            hipLaunchKernelGGL((gemm_packed_kernel<MI, NJ, SMI, SNJ>), grid, block, 0, stream, g, p.rows_small); \
+            return true;
+        PS_PACKED_PAIRS(PS_CASE)
 #undef PS_CASE
         default: return false;
     }

@@ -273,11 +273,10 @@ def test_refresh_narrow_output_many_row_tiles(P, batch, seq, bs, bl, d, kvh, hd,
 ])
 def test_refresh_packed_lists(P, batch, k_max, counts):
     """Lists without a block that are not full: their used rows are packed and
-    run in the plan for half the capacity when they fit it, in the other one
-    when not.  Entries outside the sequence are skipped, rows no entry names
-    stay byte-identical, the rest are within a bf16 step of an fp32 product."""
-    torch = pytest.importorskip("torch")
-    d, kvh, hd, seq = 512, 32, 128, k_max + 37
+    run in the smaller of the plan's two tile shapes when they are few enough,
+    in the other one when not.  Entries outside the sequence are skipped, rows
+    no entry names stay byte-identical, the rest are within a bf16 step of an
+    fp32 product."""
     g = np.random.default_rng(batch + k_max)
     half = (batch * k_max + 1) // 2
     cnt = np.zeros(batch, dtype=np.int64)
@@ -293,8 +292,14 @@ def test_refresh_packed_lists(P, batch, k_max, counts):
         for b in range(batch):
             cnt[b] = min(k_max, left)
             left -= cnt[b]
+    _check_packed(P, g, batch, k_max, cnt, 512, 32, 128)
+
+
+def _check_packed(P, g, batch, k_max, cnt, d, kvh, hd):
+    torch = pytest.importorskip("torch")
+    seq = k_max + 37
     idx = np.stack([g.permutation(seq)[:k_max] for _ in range(batch)]).astype(np.int32)
-    idx[0, 5], idx[1, 0], idx[2, 7] = -1, seq, -7
+    idx[0, 5], idx[batch // 2, 0], idx[batch - 1, 7] = -1, seq, -7
     gen = torch.Generator(device="cuda").manual_seed(k_max)
     rnd = lambda *sh: torch.randn(sh, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
     h, wk, wv = rnd(batch, seq, d), rnd(kvh * hd, d) * 0.05, rnd(kvh * hd, d) * 0.05
@@ -306,11 +311,36 @@ def test_refresh_packed_lists(P, batch, k_max, counts):
         keep = torch.ones(seq, dtype=torch.bool, device="cuda")
         keep[rows] = False
         for got, was, w in ((kc, kc0, wk), (vc, vc0, wv)):
-            assert torch.equal(got[b][keep], was[b][keep]), (b, counts)
+            assert torch.equal(got[b][keep], was[b][keep]), b
             if rows:
                 want = h[b, rows].float() @ w.float().t()
                 err = (got[b, rows].reshape(len(rows), -1).float() - want).abs().amax(1) / want.abs().amax(1)
-                assert float(err.max()) <= 5e-3, (b, counts, float(err.max()))
+                assert float(err.max()) <= 5e-3, (b, float(err.max()))
+
+
+@pytest.mark.parametrize("batch,k_max,d,kvh,pair", [
+    (3, 259, 256, 39, (192, 256, 192, 128)), (10, 365, 896, 39, (256, 128, 192, 128)),
+    (2, 322, 512, 33, (256, 128, 128, 128)), (2, 200, 1408, 33, (192, 128, 128, 128)),
+    (8, 459, 896, 26, (128, 256, 128, 128)), (70, 11, 512, 30, (256, 128, 128, 128)),
+])
+@pytest.mark.parametrize("where", ["line", "past it", "full"])
+def test_refresh_packed_shapes(P, batch, k_max, d, kvh, pair, where):
+    """Every pair of tile shapes that packed lists run in, at the number of rows
+    that is the last one for the smaller shape, one row more, and full lists;
+    more sequences than a wave has lanes."""
+    info = (ctypes.c_int * 5)()
+    assert P.lib().ps_packed_plan_info(ctypes.c_long(batch * k_max), 2 * kvh * 128, d, info)
+    assert tuple(info)[:4] == pair
+    line = min(info[4], batch * k_max - 1)
+    left = {"line": line, "past it": line + 1, "full": batch * k_max}[where]
+    g = np.random.default_rng(batch * k_max)
+    cnt = np.zeros(batch, dtype=np.int64)
+    while left > 0:                                        # uneven lists
+        b = int(g.integers(0, batch))
+        more = min(left, int(g.integers(1, 30)), k_max - int(cnt[b]))
+        cnt[b] += more
+        left -= more
+    _check_packed(P, g, batch, k_max, cnt, d, kvh, 128)
 
 
 @pytest.mark.parametrize("batch,n,d,ffn", [
