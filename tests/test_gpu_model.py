@@ -81,19 +81,21 @@ def test_embed_rmsnorm_swiglu_residual(P, dtype):
 
 
 @pytest.mark.parametrize("dtype,b,seq,rs,n,K,N", [
-    ("bf16", 3, 50, 4, 37, 384, 272),        # small-M kernel, ragged rows
-    ("bf16", 2, 300, 10, 261, 256, 400),     # rows kernel, split K, ragged tiles
+    # sizes between which the product's kernels and plans change (test_gpu_sweep names the plans it is about):
+    # ragged rows and columns, one and several sequences, short and long K
+    ("bf16", 3, 50, 4, 37, 384, 272),
+    ("bf16", 2, 300, 10, 261, 256, 400),
     ("fp32", 2, 90, 0, 90, 320, 144),
-    ("bf16", 1, 700, 0, 700, 512, 1536),     # rows kernel, several row tiles
-    ("bf16", 1, 400, 10, 385, 4096, 6480),    # 256x256-tile kernel: ragged rows and columns, K split 4
-    ("bf16", 2, 1100, 30, 1000, 4096, 2000),  # 192x192-tile kernel: ragged rows and columns, K split 2
-    ("bf16", 1, 1300, 20, 1250, 2048, 2512),  # 192x192-tile kernel: ragged rows and columns, K split 2
-    ("bf16", 3, 320, 10, 300, 4096, 3008),    # 256x192-tile kernel: 900 rows of three sequences, K split 4
-    ("bf16", 1, 460, 5, 450, 2048, 16736),    # 256x192-tile kernel, unsplit, ragged last column tile
-    ("bf16", 2, 210, 3, 200, 4096, 2800),     # rows kernel, K split 6 (too short a split for two tile rows)
-    ("bf16", 1, 4000, 0, 4000, 1024, 8000),   # tile kernel, no K split, ragged last column tile
-    ("bf16", 1, 1100, 0, 1052, 3584, 1024),   # tile kernel, K split 7 (16 stages each)
-    ("bf16", 2, 200, 20, 150, 4096, 1008),    # DMA kernel, two row tiles, ragged columns
+    ("bf16", 1, 700, 0, 700, 512, 1536),
+    ("bf16", 1, 400, 10, 385, 4096, 6480),
+    ("bf16", 2, 1100, 30, 1000, 4096, 2000),
+    ("bf16", 1, 1300, 20, 1250, 2048, 2512),
+    ("bf16", 3, 320, 10, 300, 4096, 3008),
+    ("bf16", 1, 460, 5, 450, 2048, 16736),
+    ("bf16", 2, 210, 3, 200, 4096, 2800),
+    ("bf16", 1, 4000, 0, 4000, 1024, 8000),
+    ("bf16", 1, 1100, 0, 1052, 3584, 1024),
+    ("bf16", 2, 200, 20, 150, 4096, 1008),
 ])
 def test_linear(P, dtype, b, seq, rs, n, K, N):
     torch = _torch()
@@ -148,6 +150,38 @@ def run_stack(P, index, trace=True, capture=None, **loop):
     events = []
     y, stats = den.generate(inputs.stack_prompt(cfg), trace=events.append if trace else None, capture=capture)
     return cfg, lc, ow, y, stats, events
+
+
+@pytest.mark.parametrize("mode,lo,hi", [("plain", 96, 128), ("refresh", 32, 160), ("all", 0, 160)])
+def test_forward_chained_norm_has_the_traced_bits(P, mode, lo, hi):
+    """Without a trace a layer's last residual add leaves the next layer's
+    normed rows, with one the two are passes of their own: the same bits in
+    every buffer, over several layers and two forwards in a row."""
+    from paper_2607_14107_amd import model
+    torch = _torch()
+    d, H, hd, F, V, S, b, L = 256, 4, 64, 384, 512, 160, 2, 3
+    got = []
+    for trace in (None, lambda ev: None):
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        rnd = lambda *sh: (torch.randn(sh, generator=gen, device="cuda") * 0.05).to(torch.bfloat16)  # noqa: E731
+        w = dict(tok_emb=rnd(V, d), pos_emb=rnd(S, d), w_lm=rnd(V, d),
+                 layers=[dict(w_q=rnd(d, d), w_k=rnd(d, d), w_v=rnd(d, d), w_o=rnd(d, d), w_gu=rnd(2 * F, d),
+                              w_down=rnd(d, F)) for _ in range(L)])
+        m = model.Denoiser(w, model.ModelShape(L, d, H, hd, F, V, S), b, model.LoopConfig(96, 64, 32))
+        m.y.copy_(torch.randint(0, V - 1, (b, S), generator=gen, device="cuda"))
+        for buf in [*m.hc, *m.k, *m.v]:
+            buf.copy_(rnd(*buf.shape))
+        m.eligible[:, 32:96] = 1
+        m.eligible[:, 128:160] = 1
+        m.h_cur.zero_()
+        m.drift.zero_()
+        for fwd in range(2):
+            m.forward(lo, hi, mode, (96, 32), 20 if mode == "refresh" else 0, trace=trace, fwd=fwd)
+            m.y.copy_((m.y + 7) % (V - 1))
+        n = b * (hi - lo) * d
+        got.append([m.x[:n].clone(), m.h_cur.clone(), m.drift.clone(), *(t.clone() for t in [*m.hc, *m.k, *m.v])])
+    for a, c in zip(*got):
+        assert torch.equal(a, c)
 
 
 def replay(events, cfg, lc, ow, seqs=None):
