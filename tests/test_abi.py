@@ -21,15 +21,16 @@ def L():
     return ensure_built()
 
 
-def _header_functions():
-    with open(os.path.join(ROOT, "include", "polestar.h")) as f:
+def _header_functions(header):
+    with open(os.path.join(ROOT, "include", header)) as f:
         text = f.read()
     return sorted(set(re.findall(r"\b(polestar_[a-z_]+)\s*\(", text)))
 
 
-def test_every_declared_symbol_is_exported(L):
-    names = _header_functions()
-    assert len(names) == 37, names
+@pytest.mark.parametrize("header,count", [("polestar.h", 37), ("polestar_forward.h", 5)])
+def test_every_declared_symbol_is_exported(L, header, count):
+    names = _header_functions(header)          # the second header also names one of the first
+    assert len(names) == count, names
     for n in names:
         assert hasattr(L, n), n
 
@@ -227,6 +228,66 @@ def test_model_entry_validation(L):
     gat = L.polestar_codec_gather
     assert gat(0, 1, 2, 96, 512, FAKE, FAKE, FAKE, FAKE, 8, FAKE, 8, FAKE, -1.0, FAKE, None, None) == INVALID
     assert gat(0, 1, 2, 96, 512, FAKE, FAKE, FAKE, FAKE, 8, FAKE, 8, FAKE, 1e-5, MISALIGNED, None, None) == UNSUPPORTED
+
+
+def test_project_qkv_validation(L):
+    f = L.polestar_project_qkv
+    shape = (1, 2, 4096, 32, 32, 128, 200)                    # dtype, batch, d, heads, kv heads, head dim, rows
+    ws = ps.project_qkv_workspace_size(*shape)
+    split = ps.project_qkv_workspace_size(1, 1, 4096, 4, 4, 64, 128)
+    assert split > 0                                          # a plan that splits K
+    args = [1, 2, 768, 4096, 32, 32, 128, FAKE, 512, 200, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, ws, None]
+    for i in (7, 10, 11, 12, 13, 14, 15):                     # h_cur, weights, outputs
+        a = list(args); a[i] = None
+        assert f(*a) == INVALID, i
+        a = list(args); a[i] = MISALIGNED
+        assert f(*a) == UNSUPPORTED, i
+    for i, v, want in [(0, 2, INVALID), (1, 0, INVALID), (1, 65536, UNSUPPORTED), (3, 0, INVALID),
+                       (3, 4000, UNSUPPORTED), (4, 0, INVALID), (5, 0, INVALID), (6, 96, UNSUPPORTED),
+                       (8, -1, INVALID), (8, 569, INVALID), (9, 0, INVALID), (16, MISALIGNED, UNSUPPORTED)]:
+        a = list(args); a[i] = v
+        assert f(*a) == want, (i, v)
+    a = [1, 1, 768, 4096, 4, 4, 64, FAKE, 0, 128, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, split - 1, None]
+    assert f(*a) == WORKSPACE
+    a[16], a[17] = None, 1 << 30
+    assert f(*a) == WORKSPACE
+    assert ps.project_qkv_workspace_size(1, 0, 4096, 32, 32, 128, 200) == 0
+
+
+def test_residual_rmsnorm_validation(L):
+    f = L.polestar_residual_rmsnorm
+    args = [1, 2, 10, 256, FAKE, FAKE, 1e-5, FAKE, 12, 0, None]
+    for i in (4, 5, 7):                                       # x, y, out
+        a = list(args); a[i] = None
+        assert f(*a) == INVALID, i
+        a = list(args); a[i] = MISALIGNED
+        assert f(*a) == UNSUPPORTED, i
+    for i, v, want in [(0, 2, INVALID), (1, 0, INVALID), (1, 65536, UNSUPPORTED), (2, 0, INVALID), (3, 0, INVALID),
+                       (3, 254, UNSUPPORTED), (3, 16388, UNSUPPORTED), (6, -1.0, INVALID), (6, float("nan"), INVALID),
+                       (9, 3, INVALID), (9, -1, INVALID)]:
+        a = list(args); a[i] = v
+        assert f(*a) == want, (i, v)
+
+
+def test_linear_swiglu_validation(L):
+    f = L.polestar_linear_swiglu
+    ws = L.polestar_linear_workspace_size(1, 1, 128, 512, 4096)
+    assert ws > 0
+    args = [1, 1, 200, 4096, 256, 0, 128, FAKE, FAKE, FAKE, FAKE, FAKE, ws, None]
+    for i in (7, 8, 9, 10):                                   # x, weights, gate_up, out
+        a = list(args); a[i] = None
+        assert f(*a) == INVALID, i
+        a = list(args); a[i] = MISALIGNED
+        assert f(*a) == UNSUPPORTED, i
+    for i, v, want in [(0, 2, INVALID), (1, 0, INVALID), (1, 65536, UNSUPPORTED), (3, 0, INVALID),
+                       (3, 4000, UNSUPPORTED), (4, 0, INVALID), (4, 252, UNSUPPORTED), (4, 0x40000000, UNSUPPORTED),
+                       (5, -1, INVALID), (5, 73, INVALID), (6, 0, INVALID), (11, MISALIGNED, UNSUPPORTED)]:
+        a = list(args); a[i] = v
+        assert f(*a) == want, (i, v)
+    a = list(args); a[12] = ws - 1
+    assert f(*a) == WORKSPACE
+    a[11], a[12] = None, 1 << 30
+    assert f(*a) == WORKSPACE
 
 
 def test_attention_drift_validation(L):
