@@ -151,23 +151,29 @@ static int quoted_split(bool bf16, long m_max, int N, int K) {
 // such shapes the plan that they choose is 0.7% slower than the fastest one in
 // the geometric mean, 5% at the 95th percentile and 20% at most; each shape's
 // time with every CU busy and partials at 0.32 us per MB: 1.5, 12 and 38%.
-static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_max, int N) {
-    double kt = 0.0;
+static double tile_kt(int mi, int nj) {
     switch (10 * mi + nj) {
-        case 84: kt = 1.49; break;
-        case 83: kt = 1.29; break;
-        case 64: kt = 1.25; break;
-        case 82: kt = 0.80; break;
-        case 44: kt = 0.86; break;
-        case 63: kt = 0.87; break;
-        case 62: kt = 0.62; break;
-        case 43: kt = 0.73; break;
-        case 42: kt = 0.52; break;
-        case 24: kt = 0.69; break;
-        default: kt = 0.36; break;
+        case 84: return 1.49;
+        case 83: return 1.29;
+        case 64: return 1.25;
+        case 82: return 0.80;
+        case 44: return 0.86;
+        case 63: return 0.87;
+        case 62: return 0.62;
+        case 43: return 0.73;
+        case 42: return 0.52;
+        case 24: return 0.69;
+        default: return 0.36;
     }
-    const double rounds = static_cast<double>((tiles * ks + kTargetWgs - 1) / kTargetWgs);
-    return rounds * (steps * kt + 4.0) + (ks > 1 ? 4.0 + 4.0 * ks * m_max * N * 0.4e-6 : 0.0);
+}
+static double split_cost(int ks, long m_max, int N) {
+    return ks > 1 ? 4.0 + 4.0 * ks * m_max * N * 0.4e-6 : 0.0;
+}
+static double rounds_cost(long workgroups, int steps, double kt) {
+    return static_cast<double>((workgroups + kTargetWgs - 1) / kTargetWgs) * (steps * kt + 4.0);
+}
+static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_max, int N) {
+    return rounds_cost(tiles * ks, steps, tile_kt(mi, nj)) + split_cost(ks, m_max, N);
 }
 
 // The tile kernel's plan: the tile shape and split with the least estimated
@@ -175,22 +181,31 @@ static double tile_cost(int mi, int nj, long tiles, int ks, int steps, long m_ma
 // ties.  Every split runs an even number of K tiles and at least eight.
 static void plan_tile(GemmPlan& p, long m_max, int N, int K, int max_split) {
     const int nkt = K / 64;                              // K tiles, an even number
+    struct { int ks, steps; double cost; } split[kMaxSplit];   // the splits that K allows
+    int nsplit = 0;
+    for (int ks = 1; ks <= max_split; ++ks) {
+        const int steps = 2 * ceil_div(nkt / 2, ks);
+        if (ceil_div(nkt, steps) != ks || (ks > 1 && steps < 8)) continue;
+        split[nsplit++] = {ks, steps, split_cost(ks, m_max, N)};
+    }
     double best = 1e30;
     for (int mi = 8; mi >= 2; mi -= 2) {
         for (int nj = 4; nj >= 2; --nj) {
             if (mi == 2 && nj == 3) continue;            // not instantiated
             const long tiles = static_cast<long>(ceil_div(m_max, 32 * mi)) * ceil_div(N, 64 * nj);
-            for (int ks = 1; ks <= max_split; ++ks) {
-                if (ks > 1 && tiles * (ks - 1) >= kTargetWgs) break;   // already a full round
-                const int steps = 2 * ceil_div(nkt / 2, ks);
-                if (ceil_div(nkt, steps) != ks || (ks > 1 && steps < 8)) continue;
-                const double cost = tile_cost(mi, nj, tiles, ks, steps, m_max, N);
+            const double kt = tile_kt(mi, nj);
+            for (int i = 0; i < nsplit; ++i) {
+                const auto& s = split[i];
+                if (s.ks > 1 && (tiles * (s.ks - 1) >= kTargetWgs ||   // already a full round
+                                 s.cost >= best))
+                    break;
+                const double cost = rounds_cost(tiles * s.ks, s.steps, kt) + s.cost;
                 if (cost < best) {
                     best = cost;
-                    p.ksplit = ks;
+                    p.ksplit = s.ks;
                     p.tile_mi = mi;
                     p.tile_nj = nj;
-                    p.steps_per_split = steps;
+                    p.steps_per_split = s.steps;
                 }
             }
         }
