@@ -192,17 +192,18 @@ def roofline_numbers(nbytes, flops, us, dtype):
 
 
 # Sources each call's kernels are built from (a change retires its counters).
+PRODUCT_SOURCES = ("gemm.hip", "gemm.hpp", "gemm_dev.hpp", "gemm_kernels.hpp", "gemm_tile.hip")
 CALL_SOURCES = {
-    "refresh_kv": ("gemm.hip", "gemm.hpp", "gemm_dev.hpp", "step.hip"),
-    "project_q": ("attend.hip", "gemm.hip", "gemm.hpp", "gemm_dev.hpp"),
+    "refresh_kv": PRODUCT_SOURCES + ("step.hip",),
+    "project_q": PRODUCT_SOURCES + ("attend.hip",),
     "attend": ("attend.hip", "attend_dev.hpp", "attend_ring.hip"),
     "drift": ("drift.hip", "drift_dev.hpp"),
     "select": ("select.hip", "select_dev.hpp"),
     "commit": ("commit.hip", "commit_dev.hpp"),
     "gather": ("model.hip",),
     "scatter": ("model.hip",),
-    "step": ("step.hip", "drift_dev.hpp", "select_dev.hpp", "gemm_dev.hpp", "gemm.hip", "attend_dev.hpp",
-             "attend_ring.hip", "commit_dev.hpp"),
+    "step": PRODUCT_SOURCES + ("step.hip", "drift_dev.hpp", "select_dev.hpp", "attend_dev.hpp", "attend_ring.hip",
+                               "commit_dev.hpp"),
 }
 
 

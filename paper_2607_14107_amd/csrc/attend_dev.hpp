@@ -453,7 +453,7 @@ __device__ __forceinline__ void merge_body(const AttArgs& a, int blk) {
 // LDS -- K as [key][d] rows, V^T as [d][key slot] rows -- 64 keys per step,
 // double-buffered with one barrier per step (the next step's loads are in
 // flight while the current one is computed).  Both products run on
-// v_mfma_f32_32x32x16_bf16 (on gfx950 twice the rate of the 16x16x32 form):
+// v_mfma_f32_32x32x16_bf16 (the flops of two 16x16x32 instructions each):
 // S^T = K Q^T for 32 keys x the wave's 32 queries, then O^T += V^T P^T, 16
 // keys at a time.  A lane ends S^T with 16 scores of one query (query
 // lane % 32), which are exactly the eight-key slices of P^T that the second

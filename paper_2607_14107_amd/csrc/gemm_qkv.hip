@@ -1,7 +1,8 @@
 // polestar_project_qkv: the K/V refresh and the Q projection of rows that are
 // all rewritten, as one product of three weight matrices.  In a file of its
 // own: a third matrix in the shared kernels' addressing, or its kernels in the
-// code objects that a layer step launches from, slows the smallest steps.
+// code objects that a layer step launches from, slows the smallest steps (the
+// tiny fp32 step 24.5 us with them there, 24.25 without).
 #include "gemm_kernels.hpp"
 #include "polestar_forward.h"
 

@@ -394,3 +394,17 @@ def test_dma_plan_line(L):
         assert kernel(97, n, k) == kernel(160, n, k) == 2, (n, k)
     for n, k in [(6144, 4096), (4096, 4096), (24576, 1024)]:
         assert kernel(66, n, k) == kernel(160, n, k) == 2, (n, k)
+
+
+def test_counter_digests_cover_the_sources():
+    """The digests that retire counters name every file that includes the
+    product kernels' device code, so none of them changes unseen."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2607_14107_amd", "csrc")
+    need = set()
+    for name in os.listdir(csrc):
+        with open(os.path.join(csrc, name)) as f:
+            if '#include "gemm_dev.hpp"' in f.read() or name in ("gemm_dev.hpp", "gemm.hpp", "gemm.hip"):
+                need.add(name)
+    assert need <= set(bench.CALL_SOURCES["step"]), need
+    assert need <= set(bench.CALL_SOURCES["refresh_kv"]), need
