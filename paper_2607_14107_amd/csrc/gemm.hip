@@ -369,15 +369,14 @@ static double plan_cost(const GemmPlan& p, long m, int N) {
 
 // The SwiGLU form's plan, false where two calls are faster (or the only way).
 // It runs unsplit, in the cheapest tile shape that pairs gate and up columns,
-// when its estimate and its longer epilogue (expf
-// and a division per pair: 5.5 us for a round of 256 x 256 tiles, by the pairs
-// of a lane for smaller ones) are no more above the product's own plan than the
-// separate pass costs (6.5 us for its launch and the wait behind the product,
-// and 6 bytes per feature at 5 TB/s).  4096 channels to 2 x 12288, 1024 rows:
-// 171.8 us in one launch against 192.6 in two.  The line lies near 512 rows,
-// where one launch takes 192 tiles of 256 x 256 and two take 256 of 256 x 192
-// and the pass: 94.2 against 90.5 us repeated alone, but two layers and the head
-// of a forward 1106.6 against 1109.3 us.
+// when its estimate and its longer epilogue (expf and a division per pair: 5.5
+// us for a round of 256 x 256 tiles, by the pairs of a lane for smaller ones)
+// are no more above the product's own plan than the separate pass costs (3.5 us
+// and 6 bytes per feature at 5 TB/s).  Both ways measured on 236 shapes of 65 to
+// 4000 rows: the choice is 0.4% off the faster one in the geometric mean, 15% at
+// most; two calls always 7%, one launch wherever there is one 4%.  4096 channels
+// to 2 x 12288, 1024 rows: 171.8 us in one launch against 192.6 in two; 512 rows
+// 94.2 against 90.5 (192 tiles of 256 x 256, or 256 of 256 x 192 and the pass).
 static bool swiglu_plan(const GemmPlan& plan, long m_max, int N, int K, GemmPlan& p) {
     if (!plan.tile || N % 32 != 0) return false;
     p = plan;
@@ -400,7 +399,7 @@ static bool swiglu_plan(const GemmPlan& plan, long m_max, int N, int K, GemmPlan
     }
     PS_SWIGLU_SHAPES(PS_CASE)
 #undef PS_CASE
-    return best <= plan_cost(plan, m_max, N) + 6.5 + 3.0 * m_max * N / 5e6;
+    return best <= plan_cost(plan, m_max, N) + 3.5 + 3.0 * m_max * N / 5e6;
 }
 
 bool gemm_run_swiglu(const GemmPlan& plan, GemmArgs g, hipStream_t stream) {

@@ -367,6 +367,7 @@ def test_linear_swiglu_against_its_calls(P, batch, n, d, ffn):
 @pytest.mark.parametrize("n,d,ffn,tile", [
     (65, 128, 144, (128, 128)), (529, 128, 3280, (192, 128)), (771, 128, 3280, (256, 128)),
     (1044, 128, 3280, (128, 256)), (1041, 128, 3600, (192, 256)), (1546, 128, 3616, (256, 256)),
+    (65, 2688, 8368, (128, 128)),   # unsplit, where the plain product's plan splits K
     (529, 128, 3288, None),    # 2 ffn no multiple of 32: two calls
     (200, 1536, 384, None),    # no tile kernel: two calls
 ])
