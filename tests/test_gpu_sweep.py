@@ -422,12 +422,19 @@ def test_linear_nan_bits(P, m, N, K, kernel):
     assert torch.equal(y.view(torch.int16), want)
 
 
-@pytest.mark.parametrize("dtype,batch,n,d,H,kv,hd", [
-    ("bf16", 16, 32, 512, 8, 8, 64), ("bf16", 1, 32, 1024, 8, 2, 128), ("bf16", 3, 50, 512, 4, 4, 128),
-    ("bf16", 2, 400, 256, 16, 4, 64), ("bf16", 1, 9, 256, 4, 1, 64), ("fp32", 2, 60, 128, 4, 2, 64),
+@pytest.mark.parametrize("dtype,batch,n,d,H,kv,hd,kernel,splits", [
+    ("bf16", 16, 32, 512, 8, 8, 64, 2, 1), ("bf16", 1, 32, 1024, 8, 2, 128, 0, 1), ("bf16", 3, 50, 512, 4, 4, 128, 2, 1),
+    ("bf16", 2, 400, 256, 16, 4, 64, 2, 1), ("bf16", 1, 9, 256, 4, 1, 64, 0, 1), ("fp32", 2, 60, 128, 4, 2, 64, 3, 2),
+    ("bf16", 2, 20, 4096, 32, 16, 64, 1, 8), ("bf16", 6, 32, 1536, 8, 8, 64, 1, 3), ("bf16", 2, 50, 2048, 4, 2, 64, 2, 4),
+    ("bf16", 5, 28, 4096, 32, 16, 128, 1, 4),
 ])
-def test_project_qkv_against_its_calls(P, dtype, batch, n, d, H, kv, hd):
+def test_project_qkv_against_its_calls(P, dtype, batch, n, d, H, kv, hd, kernel, splits):
+    """Each kernel that a product of three weight matrices runs on (0 small, 1
+    DMA with one and two row tiles, 2 tile, 3 rows), unsplit and split."""
     torch = pytest.importorskip("torch")
+    info = (ctypes.c_int * 4)()
+    P.lib().ps_gemm_plan_info(int(dtype == "bf16"), ctypes.c_long(batch * n), (H + 2 * kv) * hd, d, info)
+    assert (info[0], info[3]) == (kernel, splits)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(n + d)
     rnd = lambda *sh: torch.randn(sh, generator=gen, device="cuda").to(td)  # noqa: E731
